@@ -225,10 +225,7 @@ extern "C" wp_status wp_lattice_build(const wp_lattice_desc* d, const wp_allocat
     L->pk = make_pack(L->nch, nzp);
     const int nc = L->nch;
     for (int u = 0; u < nc; ++u)
-      for (int r = L->pk.lo[u]; r < L->pk.hi[u]; ++r) {
-        L->pk_src.push_back(L->pk.perm[r] * nc + L->pk.perm[u]);
-        L->pk_pos.push_back(u * nc + r);
-      }
+      for (int r = L->pk.lo[u]; r < L->pk.hi[u]; ++r) L->pk_src.push_back(L->pk.perm[r] * nc + L->pk.perm[u]);
     L->vpb = L->pk.npk;
   }
   *out = L.release();
@@ -642,11 +639,9 @@ static wp_status upload_tables(wp_lattice* L) {
       pkt[2 * nc + u] = L->pk.hi[u];
       pkt[3 * nc + u] = L->pk.off[u];
     }
-    if (!L->d_pkt.make(&L->al, pkt.size()) || !L->d_pkpos.make(&L->al, L->pk_pos.size()) ||
-        !L->d_pksrc.make(&L->al, L->pk_src.size()))
+    if (!L->d_pkt.make(&L->al, pkt.size()) || !L->d_pksrc.make(&L->al, L->pk_src.size()))
       return fail(WP_ENOMEM, "device allocation (packing tables)");
     HIPCHECK(hipMemcpy(L->d_pkt.p, pkt.data(), pkt.size() * sizeof(int), hipMemcpyHostToDevice));
-    HIPCHECK(hipMemcpy(L->d_pkpos.p, L->pk_pos.data(), L->pk_pos.size() * sizeof(int), hipMemcpyHostToDevice));
     HIPCHECK(hipMemcpy(L->d_pksrc.p, L->pk_src.data(), L->pk_src.size() * sizeof(int), hipMemcpyHostToDevice));
   }
   // fused build tables (more than 8 moments)
@@ -1141,7 +1136,7 @@ static wp_status solve_fp64(wp_lattice* L, const std::vector<double>& Elab, cons
                                      (int64_t)dG.p, (int64_t)dy.p, (int64_t)ds.p, (int64_t)dacap.p, (int64_t)dj0.p,
                                      (int64_t)dfin.p, (int64_t)pin, (int64_t)L->d_O.p, (int64_t)L->d_W.p,
                                      (int64_t)L->d_wave.p, (int64_t)L->d_rowptr.p, (int64_t)L->d_col.p,
-                                     (int64_t)val, (int64_t)order, (int64_t)L->d_pkt.p, (int64_t)L->d_pkpos.p};
+                                     (int64_t)val, (int64_t)order, (int64_t)L->d_pkt.p, L->blocks};
       HIPCHECK(graph_run(L, ws.chunk_graph[slot], key, s, [&](hipStream_t st) { return record_chunk(st, slot, T); }));
     } else {
       HIPCHECK(record_chunk(s, slot, T));

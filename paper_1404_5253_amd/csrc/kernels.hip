@@ -19,8 +19,8 @@
 //   k_step64 / k_step64m / k_step64r  per channel and column tile: t = O y, capture of
 //              e0^T O y, t *= G1, s = (v O^T) t in FP64, on the VALU or on FP64 MFMA tiles (the
 //              mixed-precision BF16 MFMA version is in kernels_mixed.hip).
-//   k_spmm / k_spmv / k_spmv_gen  block-CSR P0 times complex vectors (lanes over energies,
-//              over blocks, or over channel rows for large blocks).
+//   k_spmm / k_spmv / k_spmv_pk  block-CSR P0 times complex vectors (lanes over energies, over
+//              blocks, or over channel rows for large blocks; spmm_mfma.h: large blocks on the matrix cores).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -2805,7 +2805,8 @@ __device__ __forceinline__ float vget(const float2& v, int k) { return k ? v.y :
 __device__ __forceinline__ double vget(const double& v, int) { return v; }
 __device__ __forceinline__ float vget(const float& v, int) { return v; }
 
-// Few columns (B < 16): one wavefront per block row (rows in the order given, longest first).
+// Few columns (B <= 4, or passes of 4 on request; more columns: spmm_mfma.h): one wavefront per
+// block row (rows in the order given, longest first).
 // Lanes over (slot s, h): a slot takes one block of the pass (SL blocks per pass), lane h of the
 // slot owns the RPL channel rows RPL h .. RPL h + RPL - 1 (positions) and reads, for every block
 // column u whose stored interval holds them, RPL consecutive values. The x entries of the pass's
@@ -2965,74 +2966,6 @@ __global__ void __launch_bounds__(256) k_spmv_pk(int64_t rows, int B, int cb0, i
   }
 }
 
-// Many columns (B >= 16): lanes over columns, up to NCMAX channel accumulators per lane. The
-// wavefront stages each block's packed values into a full NC x NC block (positions, column-major)
-// in its own LDS slice, whose never-stored entries are zeroed once, and reads them back by
-// broadcast, two rows per read.
-#define NCMAX 24
-template <typename VT, typename XT, typename AT>
-__global__ void __launch_bounds__(256) k_spmm_pk(int64_t rows, int NC, int B, int cb0, int cb1,
-                                                 const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
-                                                 const VT* __restrict__ val, int npk, const int* __restrict__ pkt,
-                                                 const int* __restrict__ pk_pos, const XT* __restrict__ x,
-                                                 XT* __restrict__ y, const int32_t* __restrict__ order) {
-  __shared__ VT vs_all[4][NCMAX * NCMAX + 2];
-  VT* vs = vs_all[threadIdx.x >> 6];
-  const int64_t row = spmv_row(rows, order);
-  const int lane = threadIdx.x & 63;
-  const int c = cb0 + blockIdx.y * 64 + lane;
-  if (row < 0) return;
-  const bool live = c < cb1;
-  const int cl = live ? c : cb1 - 1;
-  const int64_t b0 = rowptr[row], b1 = rowptr[row + 1];
-  const int nc2 = NC * NC;
-  for (int t = lane; t < nc2 + 2; t += 64) vs[t] = VT(0);
-  AT ar[NCMAX], ai[NCMAX];
-#pragma unroll
-  for (int g = 0; g < NCMAX; ++g) ar[g] = ai[g] = AT(0);
-  for (int64_t e = b0; e < b1; ++e) {
-    const int cc = col[e];
-    const VT* v = val + e * npk;
-    __builtin_amdgcn_wave_barrier();
-    for (int t = lane; t < npk; t += 64) vs[pk_pos[t]] = v[t];
-    __builtin_amdgcn_wave_barrier();
-    for (int gp0 = 0; gp0 < NC; gp0 += 6) {   // six x loads in flight, then their products
-      XT xg[6];
-#pragma unroll
-      for (int u = 0; u < 6; ++u)
-        if (gp0 + u < NC) xg[u] = x[((size_t)cc * NC + pkt[gp0 + u]) * B + cl];
-#pragma unroll
-      for (int u = 0; u < 6; ++u) {
-        if (gp0 + u >= NC) break;
-        const XT xv = xg[u];
-        const VT* vg = vs + (gp0 + u) * NC;   // column u of the block: rows r = 0 .. NC - 1
-#pragma unroll
-        for (int g = 0; g < NCMAX; g += 2) {
-          if (g < NC) {
-            const AT a0 = (AT)vg[g], a1 = (g + 1 < NC) ? (AT)vg[g + 1] : AT(0);
-            ar[g] = fma(a0, (AT)xv.x, ar[g]);
-            ai[g] = fma(a0, (AT)xv.y, ai[g]);
-            if (g + 1 < NCMAX) {
-              ar[g + 1] = fma(a1, (AT)xv.x, ar[g + 1]);
-              ai[g + 1] = fma(a1, (AT)xv.y, ai[g + 1]);
-            }
-          }
-        }
-      }
-    }
-  }
-  if (!live) return;
-#pragma unroll
-  for (int g = 0; g < NCMAX; ++g) {
-    if (g < NC) {
-      XT out;
-      out.x = ar[g];
-      out.y = ai[g];
-      y[((size_t)row * NC + pkt[g]) * B + c] = out;
-    }
-  }
-}
-
 // values loaded UN block columns at a time: all NC ahead for FP32 values and vectors, else the
 // largest of 6, 5, 4, 3, 2, 1 that divides NC (register budget of FP64 data)
 template <int NC, typename VT, typename XT>
@@ -3056,7 +2989,7 @@ static void launch_spmv_pk_nc(const dim3& grid, int64_t rows, int B, int cb0, in
   const int ncols = cb1 - cb0;
   // pairs of complex FP32 columns as 16-byte loads when every chunk of 4 is whole and aligned
   const bool p2 = sizeof(XT) == 8 && B % 2 == 0 && cb0 % 2 == 0 && ncols % 4 == 0;
-  if constexpr (NC > NCMAX) {   // more than NCMAX channels: four columns per pass only
+  if constexpr (NC > 24) {   // more than 24 channels: four columns per pass only (register budget)
     launch_spmv_pk_ct<NC, 4, false, VT, XT, AT>(grid, rows, B, cb0, cb1, rowptr, col, val, npk, pkt, x, y, s, order);
   } else {
     if (ncols >= 4 && p2 && sizeof(XT) == 8)
@@ -3076,18 +3009,25 @@ hipError_t launch_spmv_gen(int64_t rows, int nch, int B, const int64_t* rowptr, 
                            const XT* x, XT* y, hipStream_t s, int cb0, int cb1, const int32_t* order,
                            const PackView& pk) {
   if (cb1 < 0) cb1 = B;
-  if (cb0 < 0 || cb1 > B || cb0 >= cb1 || rows < 1 || nch < 5 || nch > PK_MAX || !pk.pkt || !pk.pos ||
-      pk.npk < 1 || pk.npk > nch * nch)
+  if (cb0 < 0 || cb1 > B || cb0 >= cb1 || rows < 1 || nch < 5 || nch > PK_MAX || !pk.pkt || pk.npk < 1 ||
+      pk.npk > nch * nch)
     return hipErrorInvalidValue;
-  // the choice depends on B and nch only, so every launch on a given batch width sums in one order
+  // The choice depends on B, the lattice and the options only, so every launch on a given batch width
+  // sums in one order. k_spmv_pk takes passes of up to 4 columns and is the better reader of a P0 that
+  // streams from HBM: 18 channels, M = N = 150, 4 columns, 180 us in FP32 (660 MB) against 212 us for
+  // the matrix-core kernel, whose loads touch a block in 32-byte pieces, and 309 us in FP64 (1.3 GB)
+  // against 348 us. Where P0 stays in the caches, or another pass over it would be needed, the
+  // matrix-core kernel is faster: M = N = 60, 4 columns, 40 us against 54 us in FP32 and 45 us against
+  // 83 us in FP64; 14 channels, M = N = 100, 3 columns, 49 us against 87 us and 101 us against 244 us;
+  // FP32 blocks on FP64 vectors at M = N = 150: 217 us against 251 us. An explicit spmm_cols below the
+  // call's column count asks for passes of 4.
+  constexpr bool same = sizeof(XT) == 2 * sizeof(VT);
+  const int64_t line = (sizeof(VT) == 4 ? (int64_t)256 : (int64_t)800) << 20;
+  const bool passes = pk.spmm_min > 0 ? B < pk.spmm_min
+                                      : same && (B <= 2 || B == 4) &&
+                                            pk.blocks * pk.npk * (int64_t)sizeof(VT) > line;
+  if (!passes) return launch_spmm_pk(rows, nch, B, rowptr, col, val, x, y, s, cb0, cb1, order, pk);
   const dim3 grid((unsigned)spmv_blocks(rows, order));
-  if (B >= pk.spmm_min && nch <= NCMAX) {   // wide calls: lanes over the columns
-    dim3 g2 = grid;
-    g2.y = (cb1 - cb0 + 63) / 64;
-    hipLaunchKernelGGL((k_spmm_pk<VT, XT, AT>), g2, dim3(256), 0, s, rows, nch, B, cb0, cb1, rowptr, col, val, pk.npk,
-                       pk.pkt, pk.pos, x, y, order);
-    return hipGetLastError();
-  }
   switch (nch) {
 #define WP_PK_CASE(n) \
   case n: launch_spmv_pk_nc<n, VT, XT, AT>(grid, rows, B, cb0, cb1, rowptr, col, val, pk.npk, pk.pkt, x, y, s, order); break;

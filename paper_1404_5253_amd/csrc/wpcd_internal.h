@@ -230,17 +230,27 @@ hipError_t launch_init_rhs64(int M, int N, int nch, int B, const double* W, cons
                              int cb1 = -1);
 hipError_t launch_fill0(double2* p, int64_t n, hipStream_t st);
 // Device view of the packed block storage (many channels, PackDesc): npk values per block;
-// pkt[4 nc] = perm, lo, hi, off; pos[npk] = position (u nc + r) of each packed value in the full
-// column-major block of positions.
+// pkt[4 nc] = perm, lo, hi, off; spmm_min: wp_solve_opts.spmm_cols (0: the window of columns a
+// wavefront takes follows the column count).
 struct PackView {
   int npk = 0;
   const int* pkt = nullptr;
-  const int* pos = nullptr;
-  int spmm_min = 16;   // column count from which lanes run over the columns
+  int spmm_min = 0;
+  int64_t blocks = 0;   // stored blocks of the resident P0
 };
-// Block-CSR products for any storage/vector precision: lanes over columns when all B >= 16
-// columns are requested, else lanes over blocks with a wave reduction. Few channels (<= 4): full
-// column-major blocks; many channels: the packed blocks described by pk.
+// Many channels (spmm_mfma.h).
+hipError_t launch_spmm_pk(int64_t rows, int nch, int B, const int64_t* rowptr, const int32_t* col, const double* val,
+                          const double2* x, double2* y, hipStream_t s, int cb0, int cb1, const int32_t* order,
+                          const PackView& pk);
+hipError_t launch_spmm_pk(int64_t rows, int nch, int B, const int64_t* rowptr, const int32_t* col, const float* val,
+                          const float2* x, float2* y, hipStream_t s, int cb0, int cb1, const int32_t* order,
+                          const PackView& pk);
+hipError_t launch_spmm_pk(int64_t rows, int nch, int B, const int64_t* rowptr, const int32_t* col, const float* val,
+                          const double2* x, double2* y, hipStream_t s, int cb0, int cb1, const int32_t* order,
+                          const PackView& pk);
+// Block-CSR products for any storage/vector precision. Few channels (<= 4): full column-major
+// blocks, lanes over columns when B >= 16, else lanes over blocks with a wave reduction; many
+// channels: the packed blocks described by pk.
 // order: the block rows in the sequence the wavefronts take them (longest first), or nullptr
 hipError_t launch_spmv_f64(int64_t rows, int nch, int B, const int64_t* rowptr, const int32_t* col, const double* val,
                            const double2* x, double2* y, hipStream_t s, int cb0, int cb1, const int32_t* order,

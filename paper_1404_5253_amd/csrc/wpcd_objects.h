@@ -1,6 +1,7 @@
 // Handle objects of libwpcd shared by the C-ABI translation units (capi.cpp, batch.cpp).
 #pragma once
 
+#include <algorithm>
 #include <cmath>
 #include <memory>
 #include <mutex>
@@ -113,11 +114,11 @@ struct wp_lattice {
   DBuf<float> d_val32;
   wp_perm_stats stats{};
   // packed block storage for many channels (nch > 4): vpb values per stored block; per packed
-  // value its candidate-block entry (row-major g * nch + g') and its block position (u * nch + r)
+  // value its candidate-block entry (row-major g * nch + g')
   PackDesc pk;
   int vpb = 0;
-  std::vector<int> pk_src, pk_pos;
-  DBuf<int> d_pkt, d_pkpos, d_pksrc;
+  std::vector<int> pk_src;
+  DBuf<int> d_pkt, d_pksrc;
   // fused many-moment build (FusedArgs): factor-table extents, per moment its table offsets, per
   // stored value its nonzero coefficients; fz_ok when the shape fits the fused kernel
   FusedArgs fz{};
@@ -126,7 +127,7 @@ struct wp_lattice {
   DBuf<double> d_fcv;
 };
 inline PackView pk_view(const wp_lattice* L, int spmm_cols = 0) {
-  return PackView{L->pk.npk, L->d_pkt.p, L->d_pkpos.p, spmm_cols > 0 ? spmm_cols : 16};
+  return PackView{L->pk.npk, L->d_pkt.p, std::max(0, spmm_cols), L->blocks};
 }
 
 struct EnergyResult {
