@@ -300,6 +300,8 @@ extern "C" wp_status faddeev_batch_step(wp_batch* b, void* stream, int terms, in
   for (int t = 0; t < terms; ++t) {
     RotArgs ro{M, N, nch, B, L->d_O.p, L->d_wave.p, b->dG.p, b->dacap.p, b->dj0.p, b->dfin.p, nf, (int64_t)t * B * nf};
     ro.tile = b->o.step_tile;
+    ro.Of = L->d_Of.p;
+    ro.Wf = L->d_Wf.p;
     WP_LAUNCH("step64", st, launch_step64(ro, L->d_W.p, b->dy.p, b->ds.p, st));
     WP_LAUNCH("spmv64", st, launch_spmv_f64((int64_t)M * N, nch, B, L->d_rowptr.p, L->d_col.p, L->d_val64.p, b->ds.p,
                                             b->dy.p, st, 0, -1, spmv_order(L), pk_view(L, b->o.spmm_cols)));

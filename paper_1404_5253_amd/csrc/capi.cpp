@@ -483,10 +483,14 @@ wp_status wpcd::upload_waves(wp_lattice* L) {
     std::copy(L->waves[k].O.begin(), L->waves[k].O.end(), O.begin() + k * MM);
     std::copy(L->waves[k].W.begin(), L->waves[k].W.end(), W.begin() + k * MM);
   }
-  if (!L->d_O.make(&L->al, O.size()) || !L->d_W.make(&L->al, W.size()) || !L->d_wave.make(&L->al, L->nch))
+  const size_t nf = frag_elems(L->M) * L->waves.size();
+  if (!L->d_O.make(&L->al, O.size()) || !L->d_W.make(&L->al, W.size()) || !L->d_wave.make(&L->al, L->nch) ||
+      !L->d_Of.make(&L->al, nf) || !L->d_Wf.make(&L->al, nf))
     return fail(WP_ENOMEM, "device allocation (pseudostates)");
   HIPCHECK(hipMemcpy(L->d_O.p, O.data(), O.size() * 8, hipMemcpyHostToDevice));
   HIPCHECK(hipMemcpy(L->d_W.p, W.data(), W.size() * 8, hipMemcpyHostToDevice));
+  HIPCHECK(launch_pack_frag(L->M, (int)L->waves.size(), L->d_O.p, L->d_Of.p, nullptr));
+  HIPCHECK(launch_pack_frag(L->M, (int)L->waves.size(), L->d_W.p, L->d_Wf.p, nullptr));
   HIPCHECK(hipMemcpy(L->d_wave.p, L->wave_of.data(), L->nch * sizeof(int), hipMemcpyHostToDevice));
   // G1 tables
   const int nw = (int)L->waves.size(), M = L->M;
@@ -1111,6 +1115,8 @@ static wp_status solve_fp64(wp_lattice* L, const std::vector<double>& Elab, cons
       RotArgs ro{M, N, nch, B, L->d_O.p, L->d_wave.p, dG.p, dacap.p, dj0.p, dfin.p, nfin,
                  (int64_t)(slot * chunk + t) * B * nfin};
       ro.tile = o.step_tile;
+      ro.Of = L->d_Of.p;
+      ro.Wf = L->d_Wf.p;
       hipError_t e;
       {
         ProfScope ps("step64", st);

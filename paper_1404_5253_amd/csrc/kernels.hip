@@ -16,9 +16,9 @@
 //   k_row_order  SpMV work order of the final block rows (longest first).
 // Solve (step 5):
 //   k_g1       G1(E) (eqs. dg1a, dg1b) in FP64, straight into the iteration layout.
-//   k_step64 / k_step64m / k_step64r  per channel and column tile: t = O y, capture of
-//              e0^T O y, t *= G1, s = (v O^T) t in FP64, on the VALU or on FP64 MFMA tiles (the
-//              mixed-precision BF16 MFMA version is in kernels_mixed.hip).
+//   k_step64m / k_step64q / k_step64  per channel and column tile: t = O y, capture of
+//              e0^T O y, t *= G1, s = (v O^T) t in FP64, on FP64 MFMA tiles or (on request) the VALU
+//              (the mixed-precision BF16 MFMA version is in kernels_mixed.hip).
 //   k_spmm / k_spmv / k_spmv_pk  block-CSR P0 times complex vectors (lanes over energies, over
 //              blocks, or over channel rows for large blocks; spmm_mfma.h: large blocks on the matrix cores).
 #include <hip/hip_runtime.h>
@@ -1519,34 +1519,83 @@ __global__ void __launch_bounds__(256) k_step64(RotArgs r, const double* __restr
   }
 }
 
-// FP64 MFMA version (v_mfma_f64_16x16x4f64) for one channel g and 8*CT complex columns
-// (16*CT real columns, re/im adjacent): Y and T tiles [Mp][16 CT + 1] in LDS (padded rows),
-// O and v O^T read as the A operand. Operand layout of the 16x16x4 FP64 instruction: lane l holds
-// A[l%16][l/16] and B[l/16][l%16]; the result D[l/16 + 4v][l%16], v = 0..3.
+// FP64 matrix-core versions. O and v O^T come as fragment tables (launch_pack_frag): for row tile kt
+// and k step s of 8, lane l holds (A[16 kt + l%16][8 s + l/16], A[16 kt + l%16][8 s + 4 + l/16]), the A
+// operands of two steps of 4, as one contiguous kilobyte per wavefront load. (Read from the row-major
+// tables, a load touched 16 rows of 32 bytes, and the kernels waited for those loads most of their
+// time.) A workgroup takes one channel g and a tile of columns; its wavefronts share the row tiles, TPW
+// each, and keep all accumulators in registers, so that one LDS tile serves as Y and then as T. The
+// table loads run D steps ahead of the products; the first ones of v O^T are issued before the G1
+// factors are applied. The sums over i (then k) run in ascending steps of 4 in every variant.
+//   k_step64m<CT>: v_mfma_f64_16x16x4, 8 CT complex columns (16 CT real ones, re/im adjacent).
+//   k_step64q<Q>:  v_mfma_f64_4x4x4, 2 Q complex columns: the four products of an instruction are four
+//                  row quads of one 16-row tile, so the fragment tables are the same. The rate equals
+//                  that of the 16-column instruction; small grids split over more compute units.
+// Against the kernels that read row-major tables: 18 channels, M = N = 150, 4 columns (1.9 GFLOP)
+// 184 -> 79 us; 14 channels, M = N = 100, 6 columns 87 -> 35 us; 2 channels, M = N = 100, 64 columns
+// 82 -> 43 us and 1 column 13 -> 7.5 us; 1 channel, M = N = 400 (on the VALU before) 154 -> 32 us.
 typedef double d4v __attribute__((ext_vector_type(4)));
-template <int CT>
-__global__ void __launch_bounds__(256) k_step64m(RotArgs r, const double* __restrict__ Wm,
-                                                 const double2* __restrict__ y, double2* __restrict__ s_out, int Mp) {
-  extern __shared__ double shd[];
-  constexpr int RC = 16 * CT, CC = 8 * CT, RCP = RC + 1;
-  const int M = r.M, B = r.B, nch = r.nch;
-  const int ncol = r.N * B;
-  // XCD-aware order (workgroups go round robin to the 8 XCDs by linear id): each XCD takes a
-  // contiguous range of (channel, column tile) pairs, so it reads the O and vO^T tables of a few
-  // channels, which stay in its L2; the map is a bijection over the grid
+
+template <int TPW, int D>
+struct FragStream {   // fragments of TPW row tiles, D steps ahead
+  const double2* p[TPW];
+  double2 buf[D][TPW];
+  int ns;
+  __device__ void start(const double2* table, int ns_, int nt, int tile0, int tile_step, int lane) {
+    ns = ns_;
+#pragma unroll
+    for (int h = 0; h < TPW; ++h) p[h] = table + (size_t)min(tile0 + h * tile_step, nt - 1) * ns * 64 + lane;
+#pragma unroll
+    for (int u = 0; u < D; ++u)
+#pragma unroll
+      for (int h = 0; h < TPW; ++h) buf[u][h] = p[h][min(u, ns - 1) * 64];
+  }
+  // f(step, fragments) for every step in order
+  template <typename F>
+  __device__ void run(F f) {
+    int s0 = 0;
+    for (; s0 + D <= ns; s0 += D) {
+#pragma unroll
+      for (int u = 0; u < D; ++u) {
+        f(s0 + u, buf[u]);
+#pragma unroll
+        for (int h = 0; h < TPW; ++h) buf[u][h] = p[h][min(s0 + u + D, ns - 1) * 64];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < D - 1; ++u)
+      if (s0 + u < ns) f(s0 + u, buf[u]);
+  }
+};
+
+// Channel and column tile of a workgroup. XCD-aware order (workgroups go round robin to the 8 XCDs by
+// linear id): each XCD takes a contiguous range of the sequence (channel group, tile, channel of the
+// group), so it reads the tables of a few channels, which stay in its L2. A group holds the channels
+// whose entries of one cell share a 128-byte line of y, G1 and s; the map is a bijection over the grid.
+__device__ __forceinline__ void step_tile_of(int nch, int B, int& g, int& tile) {
   const int ntx = gridDim.x, T = ntx * gridDim.y;
   const int lin = blockIdx.x + ntx * blockIdx.y;
   const int xcd = lin & 7, per = T >> 3, extra = T & 7;
   const int idx = xcd * per + min(xcd, extra) + (lin >> 3);
-  const int g = idx / ntx, tile = idx - g * ntx;
-  const size_t woff = (size_t)r.wave[g] * M * M;
-  const double* O = r.A + woff;
-  const double* W = Wm + woff;
-  const int col0 = tile * CC;
-  double* YT = shd;              // [Mp][RCP]
-  double* TT = shd + Mp * RCP;   // [Mp][RCP]
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  for (int e = tid; e < CC * Mp; e += 256) {
+  const int cg = max(1, min(nch, 8 / B)), p = idx / (ntx * cg), rem = idx - p * ntx * cg;
+  const int n = min(cg, nch - p * cg);
+  tile = rem / n;
+  g = p * cg + rem - tile * n;
+}
+
+// LDS position of real column rc of row i: rows of RC doubles; with 32 columns the two halves swap
+// places in odd rows, so that the four rows a wavefront reads at once fall on all banks
+template <int RC>
+__device__ __forceinline__ int step_lds(int i, int rc) {
+  return i * RC + (RC == 32 ? rc ^ ((i & 1) << 4) : rc);
+}
+
+// the y tile of CC complex columns into LDS (zero past M and past the last column)
+template <int CC>
+__device__ __forceinline__ void step_load_y(const RotArgs& r, const double2* __restrict__ y, int g, int col0, int Mp,
+                                            double* __restrict__ YT) {
+  const int M = r.M, B = r.B, nch = r.nch, ncol = r.N * B, nthr = blockDim.x;
+  for (int e = threadIdx.x; e < CC * Mp; e += nthr) {
     int i, cc;
     if (B >= CC) {   // consecutive threads -> consecutive energies
       i = e / CC;
@@ -1561,275 +1610,263 @@ __global__ void __launch_bounds__(256) k_step64m(RotArgs r, const double* __rest
       const int jj = col / B, cb = col - jj * B;
       v = y[(((size_t)jj * M + i) * nch + g) * B + cb];
     }
-    YT[i * RCP + 2 * cc] = v.x;
-    YT[i * RCP + 2 * cc + 1] = v.y;
-  }
-  __syncthreads();
-  const int r16 = lane & 15, q4 = lane >> 4, part = r16 & 1;
-  const int nt = Mp / 16;
-  // each wavefront takes two row tiles at a time: 2 x CT independent accumulator chains
-  for (int kp = wv; 2 * kp < nt; kp += 4) {
-    d4v acc2[2][CT];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) acc2[h][ct] = d4v{0.0, 0.0, 0.0, 0.0};
-    const int krow0 = 2 * kp * 16 + r16, krow1 = krow0 + 16;
-    const double* Ok0 = O + (size_t)min(krow0, M - 1) * M;
-    const double* Ok1 = O + (size_t)min(krow1, M - 1) * M;
-#pragma unroll 4
-    for (int i0 = 0; i0 < Mp; i0 += 4) {
-      const int ic = i0 + q4;
-      const double a0 = (krow0 < M && ic < M) ? Ok0[ic] : 0.0;
-      const double a1 = (krow1 < M && ic < M) ? Ok1[ic] : 0.0;
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        const double b = YT[ic * RCP + ct * 16 + r16];
-        acc2[0][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b, acc2[0][ct], 0, 0, 0);
-        acc2[1][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b, acc2[1][ct], 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-    const int kt = 2 * kp + h;
-    if (kt >= nt) break;
-    d4v* acc = acc2[h];
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-      const int cc = ct * 8 + (r16 >> 1);
-      const int col = col0 + cc;
-      const bool live = col < ncol;
-      const int jj = live ? col / B : 0, cb = live ? col - jj * B : 0;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int k = kt * 16 + q4 + 4 * v;
-        const double val = acc[ct][v];
-        const double other = __shfl_xor(val, 1, WARP);
-        const double re = part ? other : val, im = part ? val : other;
-        double out = 0.0;
-        if (live && k < M) {
-          if (r.acap && k == 0 && part == 0 && jj == r.j0[cb]) {
-            for (int f = 0; f < r.nfin; ++f)
-              if (r.finals[f] == g) r.acap[r.acap_off + (int64_t)cb * r.nfin + f] = make_double2(re, im);
-          }
-          const double2 gv = r.G[(((size_t)jj * M + k) * nch + g) * B + cb];
-          out = part ? (re * gv.y + im * gv.x) : (re * gv.x - im * gv.y);
-        }
-        TT[k * RCP + ct * 16 + r16] = out;
-      }
-    }
-    }
-  }
-  __syncthreads();
-  double* so = reinterpret_cast<double*>(s_out);
-  for (int ip = wv; 2 * ip < nt; ip += 4) {
-    d4v acc2[2][CT];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) acc2[h][ct] = d4v{0.0, 0.0, 0.0, 0.0};
-    const int irow0 = 2 * ip * 16 + r16, irow1 = irow0 + 16;
-    const double* Wi0 = W + (size_t)min(irow0, M - 1) * M;
-    const double* Wi1 = W + (size_t)min(irow1, M - 1) * M;
-#pragma unroll 4
-    for (int k0 = 0; k0 < Mp; k0 += 4) {
-      const int kc = k0 + q4;
-      const double a0 = (irow0 < M && kc < M) ? Wi0[kc] : 0.0;
-      const double a1 = (irow1 < M && kc < M) ? Wi1[kc] : 0.0;
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        const double b = TT[kc * RCP + ct * 16 + r16];
-        acc2[0][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b, acc2[0][ct], 0, 0, 0);
-        acc2[1][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b, acc2[1][ct], 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-    const int it = 2 * ip + h;
-    if (it >= nt) break;
-    d4v* acc = acc2[h];
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-      const int cc = ct * 8 + (r16 >> 1);
-      const int col = col0 + cc;
-      if (col >= ncol) continue;
-      const int jj = col / B, cb = col - jj * B;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int i = it * 16 + q4 + 4 * v;
-        if (i < M) so[2 * ((((size_t)jj * M + i) * nch + g) * B + cb) + part] = acc[ct][v];
-      }
-    }
-    }
+    *reinterpret_cast<double2*>(YT + step_lds<2 * CC>(i, 2 * cc)) = v;
   }
 }
 
-// Small grids (one energy): one workgroup per 8 complex columns with one wavefront per 16-row
-// output tile, so that all row tiles run at once. Each lane first loads its whole A-operand
-// fragment (row kt*16 + l%16 of O, then of v O^T, every fourth column from l/16) into registers,
-// so a product is one chain of Mp/4 MFMAs with no memory waits inside.
-#define STEP64R_MAXK 32   // Mp / 4 for Mp <= 128: at most 8 wavefronts, so 256 VGPRs per lane
-// NK = Mp / 4 is a template argument so that the fragment loads and the MFMA chains are straight-line
-// code. Out-of-range fragment entries are loaded from a clamped address and kept: they meet only the
-// zero rows (i, k >= M) of the LDS tiles or produce output rows that are never stored, and every
-// entry of O and v O^T is finite, so they add exact zeros. Masking them instead would make the
-// compiler wrap each load in a branch that waits for it.
-template <int NK>
-__global__ void __launch_bounds__(512) k_step64r(RotArgs r, const double* __restrict__ Wm,
-                                                 const double2* __restrict__ y, double2* __restrict__ s_out) {
-  extern __shared__ double shd[];
-  constexpr int RCP = 17;   // 16 real columns + pad
-  constexpr int Mp = 4 * NK;
-  const int M = r.M, B = r.B, nch = r.nch;
-  const int ncol = r.N * B;
-  const int g = blockIdx.y;
-  const size_t woff = (size_t)r.wave[g] * M * M;
-  const double* O = r.A + woff;
-  const double* W = Wm + woff;
-  const int col0 = blockIdx.x * 8;
-  double* YT = shd;              // [Mp][RCP]
-  double* TT = shd + Mp * RCP;   // [Mp][RCP]
-  const int tid = threadIdx.x, lane = tid & 63, kt = tid >> 6;
+// G1 at (k, column); row 0 stands in for rows and columns past the end
+__device__ __forceinline__ double2 step_g1(const RotArgs& r, int g, int k, int jj, int cb) {
+  return r.G[(((size_t)jj * r.M + (k < r.M ? k : 0)) * r.nch + g) * r.B + cb];
+}
+// One accumulator value: (k, real column) of t, its complex partner in lane ^ 1. Captures e0^T O y and
+// returns the real or imaginary part of G1 t.
+__device__ __forceinline__ double step_scale(const RotArgs& r, int g, int k, bool live, int jj, int cb, int part,
+                                             double val, double2 gv) {
+  const double other = __shfl_xor(val, 1, WARP);
+  const double re = part ? other : val, im = part ? val : other;
+  if (!live || k >= r.M) return 0.0;
+  if (r.acap && k == 0 && part == 0 && jj == r.j0[cb]) {
+    for (int f = 0; f < r.nfin; ++f)
+      if (r.finals[f] == g) r.acap[r.acap_off + (int64_t)cb * r.nfin + f] = make_double2(re, im);
+  }
+  return part ? (re * gv.y + im * gv.x) : (re * gv.x - im * gv.y);
+}
+
+template <int CT, int TPW, int D>
+__global__ void __launch_bounds__(1024) k_step64m(RotArgs r, const double2* __restrict__ y,
+                                                 double2* __restrict__ s_out, int Mp) {
+  extern __shared__ double shd[];   // [Mp][16 CT]: Y, then T
+  constexpr int RC = 16 * CT, CC = 8 * CT;
+  const int M = r.M, B = r.B, nch = r.nch, ncol = r.N * B, nt = Mp / 16;
+  int g, tile;
+  step_tile_of(nch, B, g, tile);
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const int r16 = lane & 15, q4 = lane >> 4, part = r16 & 1;
-  const int row = kt * 16 + r16;
-  const int rowc = row < M ? row : M - 1;
-  // every global load of the kernel is issued here, so that their latencies overlap:
-  // the A fragments of O and of v O^T for this wavefront's row tile,
-  double af[NK], bf[NK];
-  {
-    const double* Ok = O + (size_t)rowc * M;
-    const double* Wi = W + (size_t)rowc * M;
+  const size_t woff = (size_t)r.wave[g] * nt * (Mp / 8) * 64;
+  const int col0 = tile * CC;
+  FragStream<TPW, D> fs;
+  fs.start(r.Of + woff, Mp / 8, nt, wv, nw, lane);
+  step_load_y<CC>(r, y, g, col0, Mp, shd);
+  __syncthreads();
+  d4v acc[TPW][CT];
+  auto product = [&]() {
 #pragma unroll
-    for (int st = 0; st < NK; ++st) {
-      const int ic = 4 * st + q4;
-      af[st] = Ok[ic < M ? ic : M - 1];
-      bf[st] = Wi[ic < M ? ic : M - 1];
-    }
-  }
-  // the two entries of the y tile that this thread stages (blockDim = 4 Mp, tile = 8 Mp entries),
-  double2 yv[2];
+    for (int h = 0; h < TPW; ++h)
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int e = tid + h * 4 * Mp;
-    const int cc = e / Mp, i = e - cc * Mp;
-    const int col = col0 + cc;
-    yv[h] = make_double2(0.0, 0.0);
-    if (i < M && col < ncol) {
-      const int jj = col / B, cb = col - jj * B;
-      yv[h] = y[(((size_t)jj * M + i) * nch + g) * B + cb];
-    }
+      for (int ct = 0; ct < CT; ++ct) acc[h][ct] = d4v{0.0, 0.0, 0.0, 0.0};
+    fs.run([&](int s, const double2 (&a)[TPW]) {
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        const double b0 = shd[step_lds<RC>(8 * s + q4, ct * 16 + r16)];
+        const double b1 = shd[step_lds<RC>(8 * s + 4 + q4, ct * 16 + r16)];
+#pragma unroll
+        for (int h = 0; h < TPW; ++h) acc[h][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[h].x, b0, acc[h][ct], 0, 0, 0);
+#pragma unroll
+        for (int h = 0; h < TPW; ++h) acc[h][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[h].y, b1, acc[h][ct], 0, 0, 0);
+      }
+    });
+  };
+  bool live[CT];
+  int jj[CT], cb[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+    const int col = col0 + ct * 8 + (r16 >> 1);
+    live[ct] = col < ncol;
+    jj[ct] = live[ct] ? col / B : 0;
+    cb[ct] = live[ct] ? col - jj[ct] * B : 0;
   }
-  // and the G1 values of the four output rows this lane owns in the first product
-  const int cc_out = r16 >> 1;
-  const int col_out = col0 + cc_out;
-  const bool live = col_out < ncol;
-  const int jj_out = live ? col_out / B : 0, cb_out = live ? col_out - jj_out * B : 0;
+  constexpr bool AHEAD = TPW * CT == 1;   // G1 in registers before the product (register budget)
   double2 gv[4];
+  if (AHEAD)
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int k = kt * 16 + q4 + 4 * v;
-    gv[v] = r.G[(((size_t)jj_out * M + (k < M ? k : M - 1)) * nch + g) * B + cb_out];
-  }
+    for (int v = 0; v < 4; ++v) gv[v] = step_g1(r, g, wv * 16 + q4 + 4 * v, jj[0], cb[0]);
+  product();
+  fs.start(r.Wf + woff, Mp / 8, nt, wv, nw, lane);
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int e = tid + h * 4 * Mp;
-    const int cc = e / Mp, i = e - cc * Mp;
-    YT[i * RCP + 2 * cc] = yv[h].x;
-    YT[i * RCP + 2 * cc + 1] = yv[h].y;
-  }
+  for (int h = 0; h < TPW; ++h)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      const int k0 = (wv + h * nw) * 16 + q4;
+      if (!AHEAD)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) gv[v] = step_g1(r, g, k0 + 4 * v, jj[ct], cb[ct]);
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        acc[h][ct][v] = step_scale(r, g, k0 + 4 * v, live[ct], jj[ct], cb[ct], part, acc[h][ct][v], gv[v]);
+      if (!AHEAD) __builtin_amdgcn_sched_barrier(0);   // one tile's G1 in flight (registers)
+    }
+  __syncthreads();   // every wavefront has read Y
+#pragma unroll
+  for (int h = 0; h < TPW; ++h)
+    if (wv + h * nw < nt)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) shd[step_lds<RC>((wv + h * nw) * 16 + q4 + 4 * v, ct * 16 + r16)] = acc[h][ct][v];
   __syncthreads();
-  d4v acc = d4v{0.0, 0.0, 0.0, 0.0};
+  product();
+  double* so = reinterpret_cast<double*>(s_out);
 #pragma unroll
-  for (int st = 0; st < NK; ++st)
-    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(af[st], YT[(4 * st + q4) * RCP + r16], acc, 0, 0, 0);
+  for (int h = 0; h < TPW; ++h)
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int k = kt * 16 + q4 + 4 * v;
-    const double val = acc[v];
-    const double other = __shfl_xor(val, 1, WARP);
-    const double re = part ? other : val, im = part ? val : other;
-    double out = 0.0;
-    if (live && k < M) {
-      if (r.acap && k == 0 && part == 0 && jj_out == r.j0[cb_out]) {
-        for (int f = 0; f < r.nfin; ++f)
-          if (r.finals[f] == g) r.acap[r.acap_off + (int64_t)cb_out * r.nfin + f] = make_double2(re, im);
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = (wv + h * nw) * 16 + q4 + 4 * v;
+        if (live[ct] && i < M) so[2 * ((((size_t)jj[ct] * M + i) * nch + g) * B + cb[ct]) + part] = acc[h][ct][v];
       }
-      out = part ? (re * gv[v].y + im * gv[v].x) : (re * gv[v].x - im * gv[v].y);
-    }
-    TT[k * RCP + r16] = out;
-  }
-  __syncthreads();
-  acc = d4v{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int st = 0; st < NK; ++st)
-    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(bf[st], TT[(4 * st + q4) * RCP + r16], acc, 0, 0, 0);
-  if (live) {
-    double* so = reinterpret_cast<double*>(s_out);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = kt * 16 + q4 + 4 * v;
-      if (i < M) so[2 * ((((size_t)jj_out * M + i) * nch + g) * B + cb_out) + part] = acc[v];
-    }
-  }
 }
 
-static size_t step64m_lds(int Mp, int ct) { return (size_t)2 * Mp * (16 * ct + 1) * sizeof(double); }
+template <int Q, int TPW, int D>
+__global__ void __launch_bounds__(1024) k_step64q(RotArgs r, const double2* __restrict__ y,
+                                                 double2* __restrict__ s_out, int Mp) {
+  extern __shared__ double shd[];   // [Mp][4 Q]: Y, then T
+  constexpr int RC = 4 * Q, CC = 2 * Q;
+  const int M = r.M, B = r.B, nch = r.nch, ncol = r.N * B, nt = Mp / 16;
+  int g, tile;
+  step_tile_of(nch, B, g, tile);
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int c4 = lane & 3, q4 = lane >> 4, part = lane & 1;
+  const int drow = ((lane >> 2) & 3) * 4 + q4;   // row of the lane's result within its 16-row tile
+  const size_t woff = (size_t)r.wave[g] * nt * (Mp / 8) * 64;
+  const int col0 = tile * CC;
+  FragStream<TPW, D> fs;
+  fs.start(r.Of + woff, Mp / 8, nt, wv, nw, lane);
+  step_load_y<CC>(r, y, g, col0, Mp, shd);
+  __syncthreads();
+  double acc[TPW][Q];
+  auto product = [&]() {
+#pragma unroll
+    for (int h = 0; h < TPW; ++h)
+#pragma unroll
+      for (int q = 0; q < Q; ++q) acc[h][q] = 0.0;
+    fs.run([&](int s, const double2 (&a)[TPW]) {
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const double b0 = shd[(8 * s + q4) * RC + 4 * q + c4], b1 = shd[(8 * s + 4 + q4) * RC + 4 * q + c4];
+#pragma unroll
+        for (int h = 0; h < TPW; ++h) acc[h][q] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[h].x, b0, acc[h][q], 0, 0, 0);
+#pragma unroll
+        for (int h = 0; h < TPW; ++h) acc[h][q] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[h].y, b1, acc[h][q], 0, 0, 0);
+      }
+    });
+  };
+  bool live[Q];
+  int jj[Q], cb[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int col = col0 + 2 * q + (c4 >> 1);
+    live[q] = col < ncol;
+    jj[q] = live[q] ? col / B : 0;
+    cb[q] = live[q] ? col - jj[q] * B : 0;
+  }
+  double2 gv[TPW][Q];   // in flight during the product
+#pragma unroll
+  for (int h = 0; h < TPW; ++h)
+#pragma unroll
+    for (int q = 0; q < Q; ++q) gv[h][q] = step_g1(r, g, (wv + h * nw) * 16 + drow, jj[q], cb[q]);
+  product();
+  fs.start(r.Wf + woff, Mp / 8, nt, wv, nw, lane);
+#pragma unroll
+  for (int h = 0; h < TPW; ++h)
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      acc[h][q] = step_scale(r, g, (wv + h * nw) * 16 + drow, live[q], jj[q], cb[q], part, acc[h][q], gv[h][q]);
+  __syncthreads();   // every wavefront has read Y
+#pragma unroll
+  for (int h = 0; h < TPW; ++h)
+    if (wv + h * nw < nt)
+#pragma unroll
+      for (int q = 0; q < Q; ++q) shd[((wv + h * nw) * 16 + drow) * RC + 4 * q + c4] = acc[h][q];
+  __syncthreads();
+  product();
+  double* so = reinterpret_cast<double*>(s_out);
+#pragma unroll
+  for (int h = 0; h < TPW; ++h)
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int i = (wv + h * nw) * 16 + drow;
+      if (live[q] && i < M) so[2 * ((((size_t)jj[q] * M + i) * nch + g) * B + cb[q]) + part] = acc[h][q];
+    }
+}
+
+// fragment tables of nw M x M matrices (row-major), zero past M
+__global__ void k_pack_frag(int M, int Mp, int nw, const double* __restrict__ A, double2* __restrict__ F) {
+  const int ns = Mp / 8, nt = Mp / 16;
+  const int64_t n = (int64_t)nw * nt * ns * 64;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= n) return;
+  const int l = (int)(t & 63);
+  int64_t q = t >> 6;
+  const int s = (int)(q % ns);
+  q /= ns;
+  const int kt = (int)(q % nt), w = (int)(q / nt);
+  const int row = 16 * kt + (l & 15), k0 = 8 * s + (l >> 4), k1 = k0 + 4;
+  const double* a = A + ((size_t)w * M + row) * M;
+  F[t] = make_double2(row < M && k0 < M ? a[k0] : 0.0, row < M && k1 < M ? a[k1] : 0.0);
+}
+
+hipError_t launch_pack_frag(int M, int nw, const double* A, double2* F, hipStream_t s) {
+  if (M < 1 || nw < 1) return hipErrorInvalidValue;
+  const int Mp = (M + 15) / 16 * 16;
+  const int64_t n = (int64_t)nw * (Mp / 16) * (Mp / 8) * 64;
+  hipLaunchKernelGGL(k_pack_frag, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, M, Mp, nw, A, F);
+  return hipGetLastError();
+}
+
+// row tiles per wavefront: the fewest that leave at most 16 wavefronts
+template <typename K>
+static hipError_t launch_step_k(K kern, const RotArgs& r, const double2* y, double2* s_out, int Mp, int cc, int tpw,
+                                hipStream_t s) {
+  const size_t lds = (size_t)Mp * 2 * cc * sizeof(double);
+  if (lds > 64 * 1024 &&
+      hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+          hipSuccess)
+    return hipErrorInvalidValue;
+  const int nt = Mp / 16, nw = (nt + tpw - 1) / tpw;
+  const dim3 grid((r.N * r.B + cc - 1) / cc, r.nch);
+  hipLaunchKernelGGL(kern, grid, dim3(64 * nw), lds, s, r, y, s_out, Mp);
+  return hipGetLastError();
+}
+template <int Q>
+static hipError_t launch_step64q(const RotArgs& r, const double2* y, double2* s_out, int Mp, hipStream_t s) {
+  const int nt = Mp / 16;
+  if (nt <= 16) return launch_step_k(k_step64q<Q, 1, 8>, r, y, s_out, Mp, 2 * Q, 1, s);
+  if (nt <= 32) return launch_step_k(k_step64q<Q, 2, 6>, r, y, s_out, Mp, 2 * Q, 2, s);
+  return launch_step_k(k_step64q<Q, 4, 2>, r, y, s_out, Mp, 2 * Q, 4, s);
+}
 
 hipError_t launch_step64(const RotArgs& r, const double* W, const double2* y, double2* s_out, hipStream_t s) {
-  if (r.M < 1 || r.N < 1 || r.B < 1 || r.nch < 1 || !r.G) return hipErrorInvalidValue;
+  if (r.M < 1 || r.M > 1024 || r.N < 1 || r.B < 1 || r.nch < 1 || !r.G || !r.Of || !r.Wf) return hipErrorInvalidValue;
   const int ncol = r.N * r.B;
-  {
-    // FP64 MFMA tiles: 16 complex columns per workgroup when the two tiles fit 64 KB of LDS and
-    // that still gives every CU a workgroup, else 8
-    const int Mp = (r.M + 15) / 16 * 16;
-    const size_t lim = 64 * 1024;
-    int ct = (step64m_lds(Mp, 2) <= lim && (int64_t)((ncol + 15) / 16) * r.nch >= 256) ? 2 : 1;
-    // an explicit choice (WP_STEP_*) that fits the lattice replaces the choice by grid size
-    const bool rows_fit = Mp / 4 <= STEP64R_MAXK && step64m_lds(Mp, 1) <= lim;
-    bool use_rows = (int64_t)((ncol + 7) / 8) * r.nch < 256 && rows_fit && step64m_lds(Mp, ct) <= lim;
-    bool use_m = !use_rows && step64m_lds(Mp, ct) <= lim && (int64_t)((ncol + 7) / 8) * r.nch >= 256;
-    if (r.tile == WP_STEP_ROWS && rows_fit) {
-      use_rows = true;
-      use_m = false;
-    } else if ((r.tile == WP_STEP_MFMA8 || r.tile == WP_STEP_MFMA16) &&
-               step64m_lds(Mp, r.tile == WP_STEP_MFMA16 ? 2 : 1) <= lim) {
-      use_rows = false;
-      use_m = true;
-      ct = r.tile == WP_STEP_MFMA16 ? 2 : 1;
-    } else if (r.tile == WP_STEP_VALU && (size_t)2 * r.M * 2 * sizeof(double2) <= lim) {
-      use_rows = use_m = false;
-    }
-    // a small grid (one energy on few channels) takes k_step64r, whose wavefronts run the row
-    // tiles of a column tile in parallel instead of one MFMA chain per tile
-    if (use_rows) {
-      // small grid: all row tiles of a column tile at once, A fragments preloaded
-      dim3 grid((ncol + 7) / 8, r.nch), block(64 * (Mp / 16));
-      const size_t sh = step64m_lds(Mp, 1);
-      switch (Mp / 16) {
-        case 1: hipLaunchKernelGGL(k_step64r<4>, grid, block, sh, s, r, W, y, s_out); break;
-        case 2: hipLaunchKernelGGL(k_step64r<8>, grid, block, sh, s, r, W, y, s_out); break;
-        case 3: hipLaunchKernelGGL(k_step64r<12>, grid, block, sh, s, r, W, y, s_out); break;
-        case 4: hipLaunchKernelGGL(k_step64r<16>, grid, block, sh, s, r, W, y, s_out); break;
-        case 5: hipLaunchKernelGGL(k_step64r<20>, grid, block, sh, s, r, W, y, s_out); break;
-        case 6: hipLaunchKernelGGL(k_step64r<24>, grid, block, sh, s, r, W, y, s_out); break;
-        case 7: hipLaunchKernelGGL(k_step64r<28>, grid, block, sh, s, r, W, y, s_out); break;
-        default: hipLaunchKernelGGL(k_step64r<32>, grid, block, sh, s, r, W, y, s_out); break;
-      }
-      return hipGetLastError();
-    }
-    if (use_m) {
-      dim3 grid((ncol + 8 * ct - 1) / (8 * ct), r.nch);
-      if (ct == 2) hipLaunchKernelGGL(k_step64m<2>, grid, dim3(256), step64m_lds(Mp, 2), s, r, W, y, s_out, Mp);
-      else hipLaunchKernelGGL(k_step64m<1>, grid, dim3(256), step64m_lds(Mp, 1), s, r, W, y, s_out, Mp);
-      return hipGetLastError();
+  const int Mp = (r.M + 15) / 16 * 16, nt = Mp / 16;
+  auto wgs = [&](int cc) { return (int64_t)((ncol + cc - 1) / cc) * r.nch; };
+  // Complex columns per workgroup: every workgroup reads both tables, so the widest tile that still
+  // gives the compute units work. Measured (us, tiles of 2 / 4 / 8 columns): 2 channels, M = N = 100, 1
+  // column 7.7 / 8.5 / 11, 4 columns 10.5 / 9.6 / 11.9, 16 columns 26 / 21 / 18.6; 1 channel, M = N = 400,
+  // 1 column 32 / 38 / 60, 2 columns 56 / 40 / 60; 18 channels, M = N = 150, 4 columns 143 / 97 / 79
+  // (16 columns per workgroup: 85). More than 512 rows: 8 columns need more registers than there are.
+  const int dflt = wgs(8) >= 240 && nt <= 32 ? 8 : wgs(4) >= 200 ? 4 : 2;
+  // an explicit choice (WP_STEP_*) that fits the lattice replaces the choice by grid size
+  const int cc = r.tile == WP_STEP_MFMA16 && nt <= 16 ? 16
+                 : r.tile == WP_STEP_MFMA8 && nt <= 32 ? 8
+                 : r.tile == WP_STEP_ROWS ? 2
+                                          : dflt;
+  if (!(r.tile == WP_STEP_VALU && (size_t)2 * r.M * 2 * sizeof(double2) <= 64 * 1024)) {
+    switch (cc) {
+      case 16: return launch_step_k(k_step64m<2, 1, 8>, r, y, s_out, Mp, 16, 1, s);
+      case 8:
+        return nt <= 16 ? launch_step_k(k_step64m<1, 1, 8>, r, y, s_out, Mp, 8, 1, s)
+                        : launch_step_k(k_step64m<1, 2, 4>, r, y, s_out, Mp, 8, 2, s);
+      case 4: return launch_step64q<2>(r, y, s_out, Mp, s);
+      default: return launch_step64q<1>(r, y, s_out, Mp, s);
     }
   }
-  // large M: the VALU version
+  // WP_STEP_VALU
   // widest column tile that fits 64 KB of LDS and still gives every CU a workgroup (the threads of a
   // wavefront then share fewer rows of O, so its loads hit fewer cache lines)
   int tc = 16;
   while (tc > 2 && ((size_t)2 * r.M * tc * sizeof(double2) > 64 * 1024 || (int64_t)(ncol / tc) * r.nch < 256)) tc >>= 1;
-  // (the large-M branch is also the one an explicit WP_STEP_VALU takes)
   const size_t shmem = (size_t)2 * r.M * tc * sizeof(double2);
   if (shmem > 64 * 1024) return hipErrorInvalidValue;
   dim3 grid((ncol + tc - 1) / tc, r.nch);

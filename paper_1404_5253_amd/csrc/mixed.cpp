@@ -152,6 +152,8 @@ wp_status wpcd::mixed_cycle(MixedWork& w, hipStream_t s, bool y_is_zero, const s
     } else {
       RotArgs ro{M, N, nch, B, L->d_O.p, L->d_wave.p, w.dG64.p, nullptr, w.dj0.p, w.dfin.p, nfin, 0};
       ro.tile = w.step_tile;
+      ro.Of = L->d_Of.p;
+      ro.Wf = L->d_Wf.p;
       {
         ProfScope ps("step64", st);
         e = launch_step64(ro, L->d_W.p, w.dy.p, w.ds64.p, st);

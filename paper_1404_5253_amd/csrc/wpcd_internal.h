@@ -221,7 +221,12 @@ struct RotArgs {
   int nfin;
   int64_t acap_off;      // offset (in double2) of this term's capture row: acap[acap_off + c*nfin + f]
   int tile = 0;          // WP_STEP_* choice of kernel (0: by shape)
+  const double2* Of = nullptr;   // fragment tables of O and v O^T (launch_pack_frag)
+  const double2* Wf = nullptr;
 };
+// Fragment tables of nw M x M matrices for the FP64 matrix-core step: frag_elems(M) double2 each.
+inline size_t frag_elems(int M) { const size_t Mp = (M + 15) / 16 * 16; return Mp * Mp / 2; }
+hipError_t launch_pack_frag(int M, int nw, const double* A, double2* F, hipStream_t s);
 // fused s = W (G1 * (O y)) with capture; r.A = O, W = v O^T (same wave layout), r.G required
 hipError_t launch_step64(const RotArgs& r, const double* W, const double2* y, double2* s_out, hipStream_t s);
 // s0 = (v O^T) e0 on the columns [cb0, cb1): the deuteron column W[:, 0] of channel g0[c] at q bin j0[c]

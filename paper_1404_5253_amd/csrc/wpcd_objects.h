@@ -61,6 +61,7 @@ struct wp_lattice {
   double eps0 = 0.0, strength = 0.0;
   // device tables
   DBuf<double> d_pe, d_qe, d_gx, d_gwx, d_gp, d_gwp, d_C, d_O, d_W;
+  DBuf<double2> d_Of, d_Wf;       // O and v O^T as matrix-core fragments (FP64 step)
   DBuf<int> d_keys, d_wave;
   // G1 tables: continuum bins per wave, bound states, quadrature rules
   DBuf<double> d_bins, d_epsb, d_ts_u, d_ts_v, d_ts_w, d_gl_x, d_gl_w;

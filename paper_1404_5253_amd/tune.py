@@ -8,7 +8,7 @@ the chosen configuration below the target on other draws of energies.
 
 A second stage tunes how the chosen configuration is launched, one choice at a time (each kept
 only if it is faster and still within the margin): the FP64 step kernel (`step_tile`: MFMA with
-8 or 16 columns per workgroup, the row-parallel MFMA kernel, or the VALU kernel), with more than
+8, 16 or 2 ("rows") columns per workgroup, or the VALU kernel), with more than
 4 channels the column count from which the block-CSR products run lanes over the columns
 (`spmm_cols`), HIP-graph replay of the term chunks / Arnoldi sweeps (`graph`), and the batch
 width (energies per call; the batch is solved in calls of that many energies).
