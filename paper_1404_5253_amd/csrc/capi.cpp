@@ -463,6 +463,8 @@ extern "C" wp_status twobody_pseudostates(wp_lattice* L, const wp_potential_desc
     L->d_O.reset();
     L->d_W.reset();
     L->d_wave.reset();
+    L->d_Ob.reset();
+    L->d_Wb.reset();
     L->pseudo = true;
     if (eps0) *eps0 = L->eps0;
     if (strength) *strength = str;

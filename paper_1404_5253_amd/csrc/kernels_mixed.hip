@@ -8,200 +8,283 @@
 
 namespace wpcd {
 
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  // round to nearest even
-  uint32_t u = __float_as_uint(f);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+// hi + lo split of a value: hi = bf16(x), lo = bf16(x - hi), each rounded to nearest even
+__device__ __forceinline__ void split_bf16(float x, __bf16& hi, __bf16& lo) {
+  hi = (__bf16)x;
+  lo = (__bf16)(x - (float)hi);
 }
 
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
 // One channel g (pair wave w) and 8*CT complex columns (16*CT real columns: re/im of each):
-//   t = O y on MFMA 16x16x16 bf16, t *= G1 (FP32), s = (v O^T) t on MFMA, s written in FP32.
+//   t = O y on MFMA 16x16x32 bf16, t *= G1 (FP32), s = (v O^T) t on MFMA, s written in FP32.
 // SPLIT = false: y, t, O and v O^T rounded to bf16 once (one product per tile);
 // SPLIT = true: every operand x is carried as hi + lo with hi = bf16(x), lo = bf16(x - hi), and
 //   a tile product is A_hi B_hi + A_hi B_lo + A_lo B_hi (16 significant bits per operand).
 // Accumulation is FP32 throughout.
-// MFMA 16x16x16 bf16 operands: lane l holds A[l%16][4(l/16)+0..3], B[4(l/16)+0..3][l%16];
+// MFMA 16x16x32 bf16 operands: lane l holds A[l%16][8(l/16)+0..7], B[8(l/16)+0..7][l%16];
 // the result D[4(l/16)+r][l%16], r = 0..3.
-template <bool SPLIT, int CT>
-__global__ void __launch_bounds__(256) k_step_bf16(RotArgsMixed r, const float2* __restrict__ y,
-                                                   float2* __restrict__ s_out) {
-  extern __shared__ uint16_t shb[];
+// The products are a small part of the time (18 channels, M = N = 150, 4 columns: 6.6 GFLOP); what counts
+// is how many loads are under way. O and v O^T come as fragment tables (launch_pack_bf16): for row tile
+// kt and k step s of 32, the hi then the lo operands of the 64 lanes, 16 bytes each, read D steps ahead
+// and first before y is staged. The wavefronts share the row tiles, TPW each, with all accumulators in
+// registers, so one LDS tile [real column][k] serves as Y and then as T; a thread stages four
+// neighbouring k of one column. Rows of the LDS tile are Kp + 8 entries long: 16 lanes reading 16
+// bytes of 16 columns then fall on all banks. Measured against two LDS tiles, row-major tables and
+// 16x16x16 products: 47 -> 28.5 us at the sizes above, 27 -> 20 us
+// at 2 channels, M = N = 100, 64 columns and 17 -> 8 us at one, 121 -> 21 us at 1 channel, M = 400,
+// N = 300, 4 columns (with events around each launch).
+template <bool SPLIT, int CT, int TPW, int D>
+__global__ void __launch_bounds__(1024) k_step_bf16(RotArgsMixed r, const float2* __restrict__ y,
+                                                    float2* __restrict__ s_out, int nt, int ns) {
+  extern __shared__ __align__(16) unsigned char shb[];
   constexpr int NP = SPLIT ? 2 : 1;
   constexpr int RC = 16 * CT;     // real columns per block
   constexpr int CC = 8 * CT;      // complex columns per block
-  const int M = r.M, Mp = r.Mp, B = r.B, nch = r.nch;
-  const int ncol = r.N * B;
-  // Workgroups are dispatched round robin to the 8 XCDs by linear id. Each XCD is given a
-  // contiguous range of (channel, column tile) pairs instead, so that it reads the O and vO^T
-  // tables of two or three channels (which then stay in its L2) rather than those of every
-  // channel; the map is a bijection over the grid.
-  const int ntx = gridDim.x, T = ntx * gridDim.y;
+  const int M = r.M, B = r.B, nch = r.nch, ncol = r.N * B;
+  const int Kp = 32 * ns, KS = Kp + 8;
+  __bf16* T = reinterpret_cast<__bf16*>(shb);   // [NP][RC][KS], real column rc = 2 cc + part
+  // Workgroups are dispatched round robin to the 8 XCDs by linear id. Each XCD is given a contiguous
+  // range of the sequence (channel group, tile, channel of the group), so that it reads the tables of
+  // a few channels (which then stay in its L2); a group holds the channels whose entries of one cell
+  // share a 128-byte line of y, G1 and s. The map is a bijection over the grid.
+  const int ntx = gridDim.x, W = ntx * gridDim.y;
   const int lin = blockIdx.x + ntx * blockIdx.y;
-  const int xcd = lin & 7, per = T >> 3, extra = T & 7;
+  const int xcd = lin & 7, per = W >> 3, extra = W & 7;
   const int idx = xcd * per + min(xcd, extra) + (lin >> 3);
-  const int g = idx / ntx, tile = idx - g * ntx;
-  const size_t woff = (size_t)r.wave[g] * Mp * Mp;
-  const uint16_t* Oh = r.A + woff;
-  const uint16_t* Ol = SPLIT ? r.A_lo + woff : nullptr;
-  const uint16_t* Wh = r.W + woff;
-  const uint16_t* Wl = SPLIT ? r.W_lo + woff : nullptr;
+  const int cg = max(1, min(nch, 16 / B)), gp = idx / (ntx * cg), rem = idx - gp * ntx * cg;
+  const int gn = min(cg, nch - gp * cg);
+  const int tile = rem / gn, g = gp * cg + rem - tile * gn;
   const int col0 = tile * CC;
-  uint16_t* YT = shb;                      // [NP][RC][Mp], real column rc = 2 cc + part
-  uint16_t* TT = shb + NP * RC * Mp;       // [NP][RC][Mp]
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  for (int e = tid; e < CC * Mp; e += 256) {
-    int cc, i;
-    if (B >= CC) {  // consecutive threads -> consecutive energies c
-      i = e / CC;
-      cc = e - i * CC;
-    } else {        // consecutive threads -> consecutive p bins i
-      cc = e / Mp;
-      i = e - cc * Mp;
-    }
-    const int col = col0 + cc;
-    float2 v = make_float2(0.f, 0.f);
-    if (i < M && col < ncol) {
-      const int jj = col / B, cb = col - jj * B;
-      v = y[(((size_t)jj * M + i) * nch + g) * B + cb];
-      if (r.yscale) {
-        const float sc = (float)r.yscale[cb];
-        v.x *= sc;
-        v.y *= sc;
-      }
-    }
-    const uint16_t hx = f2bf(v.x), hy = f2bf(v.y);
-    YT[(2 * cc) * Mp + i] = hx;
-    YT[(2 * cc + 1) * Mp + i] = hy;
-    if (SPLIT) {
-      YT[RC * Mp + (2 * cc) * Mp + i] = f2bf(v.x - bf2f(hx));
-      YT[RC * Mp + (2 * cc + 1) * Mp + i] = f2bf(v.y - bf2f(hy));
-    }
-  }
-  __syncthreads();
-  const int rc = lane & 15, quad = lane >> 4;
-  const int part = rc & 1;
-  const int nt = Mp / 16;
-  for (int kt = wv; kt < nt; kt += 4) {
-    f32x4 acc[CT];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nthr = blockDim.x, nw = nthr >> 6;
+  const int rc = lane & 15, quad = lane >> 4, part = rc & 1;
+  const size_t woff = (size_t)r.wave[g] * nt * ns * 128 + lane;
+
+  const bf16x8* p[TPW];
+  bf16x8 buf[D][TPW][NP];
+  auto fetch = [&](int u, int s) {
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // the A operand of the next tile is read while the current one is multiplied (the index is
-    // clamped at the last tile, so every read stays in the table)
-    const size_t arow = (size_t)(kt * 16 + rc) * Mp + 4 * quad;
-    bf16x4 ah_n = *reinterpret_cast<const bf16x4*>(Oh + arow), al_n;
-    if (SPLIT) al_n = *reinterpret_cast<const bf16x4*>(Ol + arow);
-    for (int it = 0; it < nt; ++it) {
-      const bf16x4 ah = ah_n;
-      bf16x4 al;
-      if (SPLIT) al = al_n;
-      const size_t an = arow + (size_t)min(it + 1, nt - 1) * 16;
-      ah_n = *reinterpret_cast<const bf16x4*>(Oh + an);
-      if (SPLIT) al_n = *reinterpret_cast<const bf16x4*>(Ol + an);
+    for (int h = 0; h < TPW; ++h)
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        const int bo = (ct * 16 + rc) * Mp + it * 16 + 4 * quad;
-        const bf16x4 bh = *reinterpret_cast<const bf16x4*>(YT + bo);
-        acc[ct] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bh, acc[ct], 0, 0, 0);
+      for (int q = 0; q < NP; ++q) buf[u][h][q] = p[h][(size_t)min(s, ns - 1) * 128 + q * 64];
+  };
+  auto start = [&](const bf16x8* table) {
+#pragma unroll
+    for (int h = 0; h < TPW; ++h) p[h] = table + woff + (size_t)min(wv + h * nw, nt - 1) * ns * 128;
+#pragma unroll
+    for (int u = 0; u < D; ++u) fetch(u, u);
+  };
+  f32x4 acc[TPW][CT];
+  auto mult = [&](int s, const bf16x8 (&a)[TPW][NP]) {
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      const __bf16* bp = T + (ct * 16 + rc) * KS + 32 * s + 8 * quad;
+      const bf16x8 bh = *reinterpret_cast<const bf16x8*>(bp);
+      bf16x8 bl;
+      if (SPLIT) bl = *reinterpret_cast<const bf16x8*>(bp + RC * KS);
+#pragma unroll
+      for (int h = 0; h < TPW; ++h) {
+        acc[h][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[h][0], bh, acc[h][ct], 0, 0, 0);
         if (SPLIT) {
-          const bf16x4 bl = *reinterpret_cast<const bf16x4*>(YT + RC * Mp + bo);
-          acc[ct] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bl, acc[ct], 0, 0, 0);
-          acc[ct] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(al, bh, acc[ct], 0, 0, 0);
+          acc[h][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[h][0], bl, acc[h][ct], 0, 0, 0);
+          acc[h][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[h][NP - 1], bh, acc[h][ct], 0, 0, 0);
         }
       }
     }
+  };
+  auto product = [&]() {
+#pragma unroll
+    for (int h = 0; h < TPW; ++h)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) acc[h][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int s0 = 0;
+    for (; s0 + D <= ns; s0 += D)
+#pragma unroll
+      for (int u = 0; u < D; ++u) {
+        mult(s0 + u, buf[u]);
+        fetch(u, s0 + u + D);
+      }
+#pragma unroll
+    for (int u = 0; u < D - 1; ++u)
+      if (s0 + u < ns) mult(s0 + u, buf[u]);
+  };
+
+  start(reinterpret_cast<const bf16x8*>(r.Of));
+  {   // y: column cc of the thread is fixed (the workgroup is a multiple of CC threads)
+    const int cc = tid % CC, col = col0 + cc;
+    const bool live = col < ncol;
+    const int jj = live ? col / B : 0, cb = live ? col - jj * B : 0;
+    const float sc = r.yscale ? (float)r.yscale[cb] : 1.f;
+    const float2* yc = y + ((size_t)jj * M * nch + g) * B + cb;
+    const size_t ist = (size_t)nch * B;
+    for (int ib = tid / CC; ib < Kp / 4; ib += nthr / CC) {
+      float2 v[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t] = live && 4 * ib + t < M ? yc[(4 * ib + t) * ist] : make_float2(0.f, 0.f);
+      bf16x4 h[2], l[2];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        __bf16 hx, lx, hy, ly;
+        split_bf16(v[t].x * sc, hx, lx);
+        split_bf16(v[t].y * sc, hy, ly);
+        h[0][t] = hx;
+        h[1][t] = hy;
+        l[0][t] = lx;
+        l[1][t] = ly;
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        __bf16* d = T + (2 * cc + q) * KS + 4 * ib;
+        *reinterpret_cast<bf16x4*>(d) = h[q];
+        if (SPLIT) *reinterpret_cast<bf16x4*>(d + RC * KS) = l[q];
+      }
+    }
+  }
+  bool live[CT];
+  int jj[CT], cb[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+    const int col = col0 + ct * 8 + (rc >> 1);
+    live[ct] = col < ncol;
+    jj[ct] = live[ct] ? col / B : 0;
+    cb[ct] = live[ct] ? col - jj[ct] * B : 0;
+  }
+  // G1 of the wavefront's rows, in flight during the product where the registers allow it
+  constexpr bool AHEAD = TPW * CT <= 2;
+  float2 gv[AHEAD ? TPW : 1][AHEAD ? CT : 1][4];
+  auto load_g = [&](int h, int ct, float2 (&v)[4]) {
+    const int k0 = (wv + h * nw) * 16 + 4 * quad;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      v[q] = r.G[(((size_t)jj[ct] * M + (k0 + q < M ? k0 + q : 0)) * nch + g) * B + cb[ct]];
+  };
+  if constexpr (AHEAD) {
+#pragma unroll
+    for (int h = 0; h < TPW; ++h)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) load_g(h, ct, gv[h][ct]);
+  }
+  __syncthreads();
+  product();
+  start(reinterpret_cast<const bf16x8*>(r.Wf));
+#pragma unroll
+  for (int h = 0; h < TPW; ++h)
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
-      const int cc = ct * 8 + (rc >> 1);
-      const int col = col0 + cc;
-      const bool live = col < ncol;
-      const int jj = live ? col / B : 0, cb = live ? col - jj * B : 0;
+      if constexpr (!AHEAD) load_g(h, ct, gv[0][0]);
+      const float2(&gq)[4] = gv[AHEAD ? h : 0][AHEAD ? ct : 0];
+      const int k0 = (wv + h * nw) * 16 + 4 * quad;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int k = kt * 16 + 4 * quad + q;
-        const float val = acc[ct][q];
+        const float val = acc[h][ct][q];
         const float other = __shfl_xor(val, 1, 64);
         const float re = part ? other : val, im = part ? val : other;
-        float out = 0.f;
-        if (live && k < M) {
-          const float2 gv = r.G[(((size_t)jj * M + k) * nch + g) * B + cb];
-          out = part ? (re * gv.y + im * gv.x) : (re * gv.x - im * gv.y);
-        }
-        const uint16_t ho = f2bf(out);
-        TT[(ct * 16 + rc) * Mp + k] = ho;
-        if (SPLIT) TT[RC * Mp + (ct * 16 + rc) * Mp + k] = f2bf(out - bf2f(ho));
+        acc[h][ct][q] = live[ct] && k0 + q < M ? (part ? (re * gq[q].y + im * gq[q].x) : (re * gq[q].x - im * gq[q].y)) : 0.f;
       }
+      if constexpr (!AHEAD) __builtin_amdgcn_sched_barrier(0);
     }
-  }
-  __syncthreads();
-  float* so = reinterpret_cast<float*>(s_out);
-  for (int itl = wv; itl < nt; itl += 4) {
-    f32x4 acc[CT];
+  __syncthreads();   // every wavefront has read Y (entries past the last row tile stay zero)
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const size_t wrow = (size_t)(itl * 16 + rc) * Mp + 4 * quad;
-    bf16x4 ah_n = *reinterpret_cast<const bf16x4*>(Wh + wrow), al_n;
-    if (SPLIT) al_n = *reinterpret_cast<const bf16x4*>(Wl + wrow);
-    for (int kt = 0; kt < nt; ++kt) {
-      const bf16x4 ah = ah_n;
-      bf16x4 al;
-      if (SPLIT) al = al_n;
-      const size_t an = wrow + (size_t)min(kt + 1, nt - 1) * 16;
-      ah_n = *reinterpret_cast<const bf16x4*>(Wh + an);
-      if (SPLIT) al_n = *reinterpret_cast<const bf16x4*>(Wl + an);
+  for (int h = 0; h < TPW; ++h)
+    if (wv + h * nw < nt)
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) {
-        const int bo = (ct * 16 + rc) * Mp + kt * 16 + 4 * quad;
-        const bf16x4 bh = *reinterpret_cast<const bf16x4*>(TT + bo);
-        acc[ct] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bh, acc[ct], 0, 0, 0);
-        if (SPLIT) {
-          const bf16x4 bl = *reinterpret_cast<const bf16x4*>(TT + RC * Mp + bo);
-          acc[ct] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bl, acc[ct], 0, 0, 0);
-          acc[ct] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(al, bh, acc[ct], 0, 0, 0);
-        }
-      }
-    }
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-      const int cc = ct * 8 + (rc >> 1);
-      const int col = col0 + cc;
-      if (col < ncol) {
-        const int jj = col / B, cb = col - jj * B;
+        bf16x4 hi, lo;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int i = itl * 16 + 4 * quad + q;
-          if (i < M) so[2 * ((((size_t)jj * M + i) * nch + g) * B + cb) + part] = acc[ct][q];
+          __bf16 a, b;
+          split_bf16(acc[h][ct][q], a, b);
+          hi[q] = a;
+          lo[q] = b;
         }
+        __bf16* d = T + (ct * 16 + rc) * KS + (wv + h * nw) * 16 + 4 * quad;
+        *reinterpret_cast<bf16x4*>(d) = hi;
+        if (SPLIT) *reinterpret_cast<bf16x4*>(d + RC * KS) = lo;
       }
-    }
-  }
+  __syncthreads();
+  product();
+  float* so = reinterpret_cast<float*>(s_out);
+#pragma unroll
+  for (int h = 0; h < TPW; ++h)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = (wv + h * nw) * 16 + 4 * quad + q;
+        if (live[ct] && i < M) so[2 * ((((size_t)jj[ct] * M + i) * nch + g) * B + cb[ct]) + part] = acc[h][ct][q];
+      }
 }
 
-size_t step_bf16_lds(int Mp, bool split, int ct) { return (size_t)2 * (split ? 2 : 1) * 16 * ct * Mp * sizeof(uint16_t); }
+// fragment tables of nw M x M FP64 matrices: per (w, row tile, k step of 32) the 64 lanes' hi operands,
+// then their lo operands, zero past M
+__global__ void k_pack_bf16(int M, int nt, int ns, int nw, const double* __restrict__ A, bf16x8* __restrict__ F) {
+  const int64_t n = (int64_t)nw * nt * ns * 64;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= n) return;
+  const int l = (int)(t & 63);
+  int64_t q = t >> 6;
+  const int64_t base = q * 128 + l;
+  const int s = (int)(q % ns);
+  q /= ns;
+  const int row = (int)(q % nt) * 16 + (l & 15), w = (int)(q / nt), k0 = 32 * s + 8 * (l >> 4);
+  bf16x8 hi, lo;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const float v = row < M && k0 + u < M ? (float)A[((size_t)w * M + row) * M + k0 + u] : 0.f;
+    __bf16 h, r;
+    split_bf16(v, h, r);
+    hi[u] = h;
+    lo[u] = r;
+  }
+  F[base] = hi;
+  F[base + 64] = lo;
+}
+
+hipError_t launch_pack_bf16(int M, int nw, const double* A, uint4* F, hipStream_t s) {
+  if (M < 1 || nw < 1) return hipErrorInvalidValue;
+  const int nt = (M + 15) / 16, ns = (M + 31) / 32;
+  const int64_t n = (int64_t)nw * nt * ns * 64;
+  hipLaunchKernelGGL(k_pack_bf16, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, M, nt, ns, nw, A,
+                     reinterpret_cast<bf16x8*>(F));
+  return hipGetLastError();
+}
+
+template <bool SPLIT, int CT, int TPW, int D>
+static hipError_t launch_step_bf16_k(const RotArgsMixed& r, const float2* y, float2* s_out, int nt, int ns,
+                                     hipStream_t s) {
+  auto kern = k_step_bf16<SPLIT, CT, TPW, D>;
+  const size_t lds = (size_t)(SPLIT ? 2 : 1) * 16 * CT * (32 * ns + 8) * 2;
+  if (lds > 64 * 1024 &&
+      hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+          hipSuccess)
+    return hipErrorInvalidValue;
+  const dim3 grid((r.N * r.B + 8 * CT - 1) / (8 * CT), r.nch);
+  hipLaunchKernelGGL(kern, grid, dim3(64 * ((nt + TPW - 1) / TPW)), lds, s, r, y, s_out, nt, ns);
+  return hipGetLastError();
+}
+
+// Row tiles per wavefront: the fewest that leave at most 16 wavefronts.
+template <bool SPLIT, int CT>
+static hipError_t launch_step_bf16_ct(const RotArgsMixed& r, const float2* y, float2* s_out, hipStream_t s) {
+  const int nt = (r.M + 15) / 16, ns = (r.M + 31) / 32;
+  if (nt <= 16) return launch_step_bf16_k<SPLIT, CT, 1, 4>(r, y, s_out, nt, ns, s);
+  if (nt <= 32) return launch_step_bf16_k<SPLIT, CT, 2, 2>(r, y, s_out, nt, ns, s);
+  return launch_step_bf16_k<SPLIT, 1, 4, 2>(r, y, s_out, nt, ns, s);
+}
 
 hipError_t launch_step_bf16(const RotArgsMixed& r, const float2* y, float2* s_out, hipStream_t s) {
-  if (r.M < 1 || r.Mp < r.M || r.Mp % 16 || r.N < 1 || r.B < 1 || r.nch < 1 || !r.G || !r.A || !r.W)
+  // split operands up to 512 rows, single ones up to 1024
+  if (r.M < 1 || r.M > (r.split ? 512 : 1024) || r.N < 1 || r.B < 1 || r.nch < 1 || !r.G || !r.Of || !r.Wf)
     return hipErrorInvalidValue;
-  const bool split = r.A_lo != nullptr;
-  if (split && !r.W_lo) return hipErrorInvalidValue;
-  const size_t lim = 64 * 1024;
-  const int ct = step_bf16_lds(r.Mp, split, 2) <= lim ? 2 : 1;
-  const size_t shmem = step_bf16_lds(r.Mp, split, ct);
-  if (shmem > lim) return hipErrorInvalidValue;
-  dim3 grid((r.N * r.B + 8 * ct - 1) / (8 * ct), r.nch);
-  if (split) {
-    if (ct == 2) hipLaunchKernelGGL((k_step_bf16<true, 2>), grid, dim3(256), shmem, s, r, y, s_out);
-    else hipLaunchKernelGGL((k_step_bf16<true, 1>), grid, dim3(256), shmem, s, r, y, s_out);
-  } else {
-    if (ct == 2) hipLaunchKernelGGL((k_step_bf16<false, 2>), grid, dim3(256), shmem, s, r, y, s_out);
-    else hipLaunchKernelGGL((k_step_bf16<false, 1>), grid, dim3(256), shmem, s, r, y, s_out);
-  }
-  return hipGetLastError();
+  // 16 columns per workgroup read the tables half as often as 8, which wins once the row tiles of all
+  // workgroups fill the device (us, 8 / 16 columns, split): 2 channels, M = N = 100, 8 columns 8.5 / 9.9,
+  // 64 columns 24.5 / 20.4; 18 channels, M = N = 150, 4 columns 36 / 28.5; 1 channel, M = 400, N = 300,
+  // 4 columns 20.7 / 24.8, 8 columns 35 / 25
+  const bool wide = (int64_t)((r.N * r.B + 15) / 16) * r.nch * ((r.M + 15) / 16) >= 2400;
+  if (r.split) return wide ? launch_step_bf16_ct<true, 2>(r, y, s_out, s) : launch_step_bf16_ct<true, 1>(r, y, s_out, s);
+  return wide ? launch_step_bf16_ct<false, 2>(r, y, s_out, s) : launch_step_bf16_ct<false, 1>(r, y, s_out, s);
 }
 
 // ------------------------------------------------------------------ refinement helpers (FP64)

@@ -25,45 +25,15 @@
 
 using namespace wpcd;
 
-static uint16_t host_bf16(double d) {
-  float f = (float)d;
-  uint32_t u;
-  std::memcpy(&u, &f, 4);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-
 wp_status wpcd::ensure_mixed(wp_lattice* L, hipStream_t s) {
   if (wp_status st = upload_waves(L)) return st;
-  const int M = L->M;
   if (!L->d_Ob.p) {
-    // bf16 copies of O and v O^T (hi) and of their rounding remainders (lo), padded to Mp
-    const int Mp = (M + 15) / 16 * 16;
-    const size_t MM = (size_t)Mp * Mp;
-    const size_t n = MM * L->waves.size();
-    std::vector<uint16_t> Oh(n, 0), Ol(n, 0), Wh(n, 0), Wl(n, 0);
-    auto split = [](double d, uint16_t& hi, uint16_t& lo) {
-      hi = host_bf16(d);
-      uint32_t u = (uint32_t)hi << 16;
-      float f;
-      std::memcpy(&f, &u, 4);
-      lo = host_bf16((double)((float)d - f));
-    };
-    for (size_t w = 0; w < L->waves.size(); ++w)
-      for (int r = 0; r < M; ++r)
-        for (int c = 0; c < M; ++c) {
-          const size_t k = w * MM + (size_t)r * Mp + c;
-          split(L->waves[w].O[(size_t)r * M + c], Oh[k], Ol[k]);
-          split(L->waves[w].W[(size_t)r * M + c], Wh[k], Wl[k]);
-        }
-    if (!L->d_Ob.make(&L->al, n) || !L->d_Wb.make(&L->al, n) || !L->d_Ob_lo.make(&L->al, n) ||
-        !L->d_Wb_lo.make(&L->al, n))
-      return fail(WP_ENOMEM, "device allocation (bf16 blocks)");
-    HIPCHECK(hipMemcpy(L->d_Ob.p, Oh.data(), n * 2, hipMemcpyHostToDevice));
-    HIPCHECK(hipMemcpy(L->d_Wb.p, Wh.data(), n * 2, hipMemcpyHostToDevice));
-    HIPCHECK(hipMemcpy(L->d_Ob_lo.p, Ol.data(), n * 2, hipMemcpyHostToDevice));
-    HIPCHECK(hipMemcpy(L->d_Wb_lo.p, Wl.data(), n * 2, hipMemcpyHostToDevice));
-    L->Mp = Mp;
+    const int nw = (int)L->waves.size();
+    const size_t n = frag_bf16_elems(L->M) * nw;
+    if (!L->d_Wb.make(&L->al, n) || !L->d_Ob.make(&L->al, n)) return fail(WP_ENOMEM, "device allocation (bf16 blocks)");
+    HIPCHECK(launch_pack_bf16(L->M, nw, L->d_O.p, L->d_Ob.p, s));
+    HIPCHECK(launch_pack_bf16(L->M, nw, L->d_W.p, L->d_Wb.p, s));
+    HIPCHECK(hipStreamSynchronize(s));   // ready for later calls, on any stream
   }
   if (!L->d_val32.p) {
     const int64_t n = L->blocks * L->vpb;
@@ -175,8 +145,7 @@ wp_status wpcd::mixed_cycle(MixedWork& w, hipStream_t s, bool y_is_zero, const s
     if ((e = launch_scale_d2f(D, B, w.nrm.p, w.dr.p, w.V.p, w.scl.p, st)) != hipSuccess) return e;
     ArnoldiArgs aa{R,         nch,     B,      m,    0,          L->d_rowptr.p, L->d_col.p, L->d_val32.p,
                    spmv_order(L), w.V.p, DB,    w.scl.p, w.H.p, w.part.p, kNblk, pk_view(L, w.spmm_cols)};
-    RotArgsMixed rm{M,          N, nch, B, L->d_Ob.p, w.split ? L->d_Ob_lo.p : nullptr, L->d_Wb.p,
-                    w.split ? L->d_Wb_lo.p : nullptr, L->Mp, L->d_wave.p, w.dG32.p, nullptr};
+    RotArgsMixed rm{M, N, nch, B, L->d_Ob.p, L->d_Wb.p, w.split, L->d_wave.p, w.dG32.p, nullptr};
     for (int j = 0; j < m; ++j) {
       aa.j = j;
       rm.yscale = w.scl.p + (size_t)j * B;
@@ -200,8 +169,8 @@ wp_status wpcd::mixed_cycle(MixedWork& w, hipStream_t s, bool y_is_zero, const s
         (int64_t)w.dy.p,    (int64_t)w.ds64.p, (int64_t)w.dKy.p, (int64_t)w.dG64.p, (int64_t)w.dG32.p,
         (int64_t)w.dj0.p,   (int64_t)w.dfin.p, (int64_t)w.part.p, (int64_t)w.nrm.p, (int64_t)w.V.p,
         (int64_t)w.scl.p,   (int64_t)w.H.p, (int64_t)w.t32.p, (int64_t)w.kv32.p, (int64_t)L->d_O.p,
-        (int64_t)L->d_W.p,  (int64_t)L->d_wave.p, (int64_t)L->d_Ob.p, (int64_t)L->d_Ob_lo.p, (int64_t)L->d_Wb.p,
-        (int64_t)L->d_Wb_lo.p, (int64_t)L->d_rowptr.p, (int64_t)L->d_col.p, (int64_t)L->d_val32.p,
+        (int64_t)L->d_W.p,  (int64_t)L->d_wave.p, (int64_t)L->d_Ob.p, (int64_t)L->d_Wb.p,
+        (int64_t)L->d_rowptr.p, (int64_t)L->d_col.p, (int64_t)L->d_val32.p,
         (int64_t)spmv_order(L), (int64_t)L->d_pkt.p, L->blocks};
     HIPCHECK(graph_run(L, w.sweep_graph[y_is_zero ? 0 : 1], key, s, record_sweep));
   } else {

@@ -302,16 +302,17 @@ hipError_t launch_g1(const G1Args& g, hipStream_t s);
 // Mixed precision (FP32 P0, BF16 blocks on MFMA with FP32 accumulation, FP32 vectors)
 struct RotArgsMixed {
   int M, N, nch, B;
-  const uint16_t* A;      // O in bf16: [nwave][Mp][Mp] row-major, zero padded
-  const uint16_t* A_lo;   // bf16(O - A) for the split representation, or nullptr
-  const uint16_t* W;      // v O^T in bf16, same layout
-  const uint16_t* W_lo;   // bf16(v O^T - W) or nullptr
-  int Mp;                 // M rounded up to a multiple of 16
+  const uint4* Of;        // O and v O^T in bf16 as matrix-core fragments (launch_pack_bf16)
+  const uint4* Wf;
+  bool split;             // operands as hi + lo pairs
   const int* wave;
   const float2* G;        // G1 in FP32 [j][k][g][c]
   const double* yscale;   // per-column factor applied to y on load (nullptr: 1)
 };
-// s = W (G1 * (O y)) on MFMA (split representation when A_lo / W_lo are given)
+// Fragment tables of nw M x M matrices, hi and lo parts: frag_bf16_elems(M) uint4 each.
+inline size_t frag_bf16_elems(int M) { return (size_t)((M + 15) / 16) * ((M + 31) / 32) * 128; }
+hipError_t launch_pack_bf16(int M, int nw, const double* A, uint4* F, hipStream_t s);
+// s = W (G1 * (O y)) on MFMA
 hipError_t launch_step_bf16(const RotArgsMixed& r, const float2* y, float2* s_out, hipStream_t s);
 hipError_t launch_cvt_d2f(int64_t n, const double2* in, float2* out, hipStream_t s);
 hipError_t launch_cvt_d2f_cols(int64_t rows, int B, int c0, int c1, const double2* in, float2* out, hipStream_t s);

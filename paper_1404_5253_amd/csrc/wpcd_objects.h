@@ -67,9 +67,8 @@ struct wp_lattice {
   DBuf<double> d_bins, d_epsb, d_ts_u, d_ts_v, d_ts_w, d_gl_x, d_gl_w;
   DBuf<int> d_nb;
   int nts = 0, ngl = 0;
-  // mixed precision: bf16 copies of O and v O^T (padded to Mp), FP32 P0 values
-  int Mp = 0;
-  DBuf<uint16_t> d_Ob, d_Wb, d_Ob_lo, d_Wb_lo;
+  // mixed precision: O and v O^T in bf16 (hi and lo parts) as matrix-core fragments
+  DBuf<uint4> d_Ob, d_Wb;
   // P0
   bool have_P = false;
   int prec = WP_P_FP64;
