@@ -3057,12 +3057,14 @@ hipError_t launch_spmv_gen(int64_t rows, int nch, int B, const int64_t* rowptr, 
   // matrix-core kernel is faster: M = N = 60, 4 columns, 40 us against 54 us in FP32 and 45 us against
   // 83 us in FP64; 14 channels, M = N = 100, 3 columns, 49 us against 87 us and 101 us against 244 us;
   // FP32 blocks on FP64 vectors at M = N = 150: 217 us against 251 us. An explicit spmm_cols below the
-  // call's column count asks for passes of 4.
+  // call's column count asks for passes of 4. PackView.one_order: passes below 16 columns, then the
+  // 32-column window with a row's blocks summed in sequence (the same sums as one lane per column).
   constexpr bool same = sizeof(XT) == 2 * sizeof(VT);
   const int64_t line = (sizeof(VT) == 4 ? (int64_t)256 : (int64_t)800) << 20;
-  const bool passes = pk.spmm_min > 0 ? B < pk.spmm_min
-                                      : same && (B <= 2 || B == 4) &&
-                                            pk.blocks * pk.npk * (int64_t)sizeof(VT) > line;
+  const bool passes = pk.one_order     ? B < (pk.spmm_min > 0 ? pk.spmm_min : 16) || nch > 24
+                      : pk.spmm_min > 0 ? B < pk.spmm_min
+                                        : same && (B <= 2 || B == 4) &&
+                                              pk.blocks * pk.npk * (int64_t)sizeof(VT) > line;
   if (!passes) return launch_spmm_pk(rows, nch, B, rowptr, col, val, x, y, s, cb0, cb1, order, pk);
   const dim3 grid((unsigned)spmv_blocks(rows, order));
   switch (nch) {

@@ -10,6 +10,7 @@ namespace wpcd {
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // hi + lo split of a value: hi = bf16(x), lo = bf16(x - hi), each rounded to nearest even
@@ -24,8 +25,10 @@ __device__ __forceinline__ void split_bf16(float x, __bf16& hi, __bf16& lo) {
 // SPLIT = true: every operand x is carried as hi + lo with hi = bf16(x), lo = bf16(x - hi), and
 //   a tile product is A_hi B_hi + A_hi B_lo + A_lo B_hi (16 significant bits per operand).
 // Accumulation is FP32 throughout.
-// MFMA 16x16x32 bf16 operands: lane l holds A[l%16][8(l/16)+0..7], B[8(l/16)+0..7][l%16];
-// the result D[4(l/16)+r][l%16], r = 0..3.
+// MFMA operands: lane l holds row l%16 of A and column l%16 of B at the 8 k of its quarter q = l/16; within
+// a block of 32 these are 4q .. 4q+3 and 16+4q .. 16+4q+3, the order in which the fragment tables and the
+// LDS tile hold them, so that one 16-byte read serves one 16x16x32 product (SPLIT) or two 16x16x16
+// products in ascending k. The result is D[4(l/16)+r][l%16], r = 0..3.
 // The products are a small part of the time (18 channels, M = N = 150, 4 columns: 6.6 GFLOP); what counts
 // is how many loads are under way. O and v O^T come as fragment tables (launch_pack_bf16): for row tile
 // kt and k step s of 32, the hi then the lo operands of the 64 lanes, 16 bytes each, read D steps ahead
@@ -86,10 +89,16 @@ __global__ void __launch_bounds__(1024) k_step_bf16(RotArgsMixed r, const float2
       if (SPLIT) bl = *reinterpret_cast<const bf16x8*>(bp + RC * KS);
 #pragma unroll
       for (int h = 0; h < TPW; ++h) {
-        acc[h][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[h][0], bh, acc[h][ct], 0, 0, 0);
-        if (SPLIT) {
+        if constexpr (SPLIT) {
+          acc[h][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[h][0], bh, acc[h][ct], 0, 0, 0);
           acc[h][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[h][0], bl, acc[h][ct], 0, 0, 0);
-          acc[h][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[h][NP - 1], bh, acc[h][ct], 0, 0, 0);
+          acc[h][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[h][1], bh, acc[h][ct], 0, 0, 0);
+        } else {
+          const s16x8 x = __builtin_bit_cast(s16x8, a[h][0]), z = __builtin_bit_cast(s16x8, bh);
+          acc[h][ct] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_shufflevector(x, x, 0, 1, 2, 3),
+                                                                 __builtin_shufflevector(z, z, 0, 1, 2, 3), acc[h][ct], 0, 0, 0);
+          acc[h][ct] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_shufflevector(x, x, 4, 5, 6, 7),
+                                                                 __builtin_shufflevector(z, z, 4, 5, 6, 7), acc[h][ct], 0, 0, 0);
         }
       }
     }
@@ -136,7 +145,7 @@ __global__ void __launch_bounds__(1024) k_step_bf16(RotArgsMixed r, const float2
       }
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
-        __bf16* d = T + (2 * cc + q) * KS + 4 * ib;
+        __bf16* d = T + (2 * cc + q) * KS + 32 * (ib >> 3) + 8 * (ib & 3) + (ib & 4);
         *reinterpret_cast<bf16x4*>(d) = h[q];
         if (SPLIT) *reinterpret_cast<bf16x4*>(d + RC * KS) = l[q];
       }
@@ -181,7 +190,11 @@ __global__ void __launch_bounds__(1024) k_step_bf16(RotArgsMixed r, const float2
         const float val = acc[h][ct][q];
         const float other = __shfl_xor(val, 1, 64);
         const float re = part ? other : val, im = part ? val : other;
-        acc[h][ct][q] = live[ct] && k0 + q < M ? (part ? (re * gq[q].y + im * gq[q].x) : (re * gq[q].x - im * gq[q].y)) : 0.f;
+        // one rounded product, then one fused step, spelled out: with single BF16 operands a different
+        // last bit of t here and there already makes another refinement path
+        const float pi = re * gq[q].y, pr = im * gq[q].y;
+        const float out = part ? fmaf(im, gq[q].x, pi) : fmaf(re, gq[q].x, -pr);
+        acc[h][ct][q] = live[ct] && k0 + q < M ? out : 0.f;
       }
       if constexpr (!AHEAD) __builtin_amdgcn_sched_barrier(0);
     }
@@ -199,7 +212,8 @@ __global__ void __launch_bounds__(1024) k_step_bf16(RotArgsMixed r, const float2
           hi[q] = a;
           lo[q] = b;
         }
-        __bf16* d = T + (ct * 16 + rc) * KS + (wv + h * nw) * 16 + 4 * quad;
+        const int tl = wv + h * nw;
+        __bf16* d = T + (ct * 16 + rc) * KS + 32 * (tl >> 1) + 8 * quad + 4 * (tl & 1);
         *reinterpret_cast<bf16x4*>(d) = hi;
         if (SPLIT) *reinterpret_cast<bf16x4*>(d + RC * KS) = lo;
       }
@@ -228,11 +242,12 @@ __global__ void k_pack_bf16(int M, int nt, int ns, int nw, const double* __restr
   const int64_t base = q * 128 + l;
   const int s = (int)(q % ns);
   q /= ns;
-  const int row = (int)(q % nt) * 16 + (l & 15), w = (int)(q / nt), k0 = 32 * s + 8 * (l >> 4);
+  const int row = (int)(q % nt) * 16 + (l & 15), w = (int)(q / nt), k0 = 32 * s + 4 * (l >> 4);
   bf16x8 hi, lo;
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
-    const float v = row < M && k0 + u < M ? (float)A[((size_t)w * M + row) * M + k0 + u] : 0.f;
+    const int k = k0 + (u & 3) + 4 * (u & 4);
+    const float v = row < M && k < M ? (float)A[((size_t)w * M + row) * M + k] : 0.f;
     __bf16 h, r;
     split_bf16(v, h, r);
     hi[u] = h;

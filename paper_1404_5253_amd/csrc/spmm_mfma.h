@@ -362,7 +362,7 @@ inline bool shared_rows(int64_t rows) { return rows < 16384; }
 
 template <int NC>
 void launch_nc(int64_t rows, int B, int cb0, int cb1, const int64_t* rowptr, const int32_t* col, const float* val, int npk,
-               const int* pkt, const float2* x, float2* y, const int32_t* order, int window, hipStream_t s) {
+               const int* pkt, const float2* x, float2* y, const int32_t* order, int window, bool one_order, hipStream_t s) {
   const float* xr = reinterpret_cast<const float*>(x);
   float* yr = reinterpret_cast<float*>(y);
 #define WP_W(cw, wr)                                                                                           \
@@ -376,6 +376,7 @@ void launch_nc(int64_t rows, int B, int cb0, int cb1, const int64_t* rowptr, con
   else if (window <= 4) WP_W(4, 1)
   else if (window <= 8 && sh) WP_W(8, 4)
   else if (window <= 8) WP_W(8, 1)
+  else if (one_order) WP_W(32, 1)
   else if (window <= 16) WP_W(16, 4)
   else WP_W(32, 4)
 #undef WP_W
@@ -383,7 +384,7 @@ void launch_nc(int64_t rows, int B, int cb0, int cb1, const int64_t* rowptr, con
 
 template <int NC, typename VT>
 void launch_nc(int64_t rows, int B, int cb0, int cb1, const int64_t* rowptr, const int32_t* col, const VT* val, int npk,
-               const int* pkt, const double2* x, double2* y, const int32_t* order, int window, hipStream_t s) {
+               const int* pkt, const double2* x, double2* y, const int32_t* order, int window, bool one_order, hipStream_t s) {
 #define WP_W(gb, h, wr)                                                                                       \
   {                                                                                                           \
     static const int per_cu = resident(k_spmm_f64<NC, gb, h, wr, VT>);                                        \
@@ -396,6 +397,7 @@ void launch_nc(int64_t rows, int B, int cb0, int cb1, const int64_t* rowptr, con
   else if (window <= 4) WP_W(4, 1, 1)
   else if (window <= 8 && sh) WP_W(4, 2, 4)
   else if (window <= 8) WP_W(4, 2, 1)
+  else if (one_order) WP_W(1, 2, 1)
   else if (window <= 16) WP_W(1, 1, 4)
   else WP_W(1, 2, 4)
 #undef WP_W
@@ -409,10 +411,10 @@ hipError_t launch(int64_t rows, int nch, int B, const int64_t* rowptr, const int
       pk.npk > nch * nch)
     return hipErrorInvalidValue;
   // the choice depends on B and the options only, so every launch on a given batch width sums in one order
-  const int window = spmm_window(B, pk.spmm_min);
+  const int window = pk.one_order ? 32 : spmm_window(B, pk.spmm_min);
   switch (nch) {
 #define WP_NC(n) \
-  case n: launch_nc<n>(rows, B, cb0, cb1, rowptr, col, val, pk.npk, pk.pkt, x, y, order, window, s); break;
+  case n: launch_nc<n>(rows, B, cb0, cb1, rowptr, col, val, pk.npk, pk.pkt, x, y, order, window, pk.one_order, s); break;
     WP_NC(5) WP_NC(6) WP_NC(7) WP_NC(8) WP_NC(9) WP_NC(10) WP_NC(11) WP_NC(12) WP_NC(13) WP_NC(14)
     WP_NC(15) WP_NC(16) WP_NC(17) WP_NC(18) WP_NC(19) WP_NC(20) WP_NC(21) WP_NC(22) WP_NC(23) WP_NC(24)
     WP_NC(25) WP_NC(26) WP_NC(27) WP_NC(28) WP_NC(29) WP_NC(30) WP_NC(31) WP_NC(32)

@@ -242,6 +242,11 @@ struct PackView {
   const int* pkt = nullptr;
   int spmm_min = 0;
   int64_t blocks = 0;   // stored blocks of the resident P0
+  // products of the unsplit mixed mode: one order of summation per column count. Its BF16 operands
+  // are rounded once, so another order of the sums moves some of them to the other neighbour and
+  // the refinement takes another path: with several orders in use, solves that stop at an estimate of
+  // 1e-10 differed by up to 1.5e-9, with one they do not.
+  bool one_order = false;
 };
 // Many channels (spmm_mfma.h).
 hipError_t launch_spmm_pk(int64_t rows, int nch, int B, const int64_t* rowptr, const int32_t* col, const double* val,
