@@ -657,10 +657,14 @@ __device__ __forceinline__ double wsum64(double v) {
   return v;
 }
 
-// One wavefront per output (i, c), lanes over the blocks in a fixed order.
+// One wavefront per output (i, c), lanes over the blocks in a fixed order; a lane's partials (at most
+// ARN_MAXBLK / 64) are all read before they are added (one after another they cost 16 memory latencies,
+// 7 us a launch; 3 us now).
 // mode 0: out[i][c] = scl[i][c] * sum_blk part[blk][i][c]       (Hessenberg column, i < nv)
 // mode 1: n = sqrt(sum_blk part[blk][0][c].x); out[0][c] = n;    (subdiagonal entry)
 //         scl_next[c] = 1 / n (0 for a zero vector)
+#define ARN_MAXBLK 1024
+template <int PL>
 __global__ void __launch_bounds__(256) k_arn_finish(int nblk, int B, int nv, const double2* __restrict__ part,
                                                     const double* __restrict__ scl, double2* __restrict__ out,
                                                     double* __restrict__ scl_next, int mode) {
@@ -668,11 +672,17 @@ __global__ void __launch_bounds__(256) k_arn_finish(int nblk, int B, int nv, con
   const int lane = threadIdx.x & 63;
   if (t >= nv * B) return;
   const int i = t / B, c = t - i * B;
+  double2 v[PL];
+#pragma unroll
+  for (int u = 0; u < PL; ++u) {
+    const int b = lane + 64 * u;
+    v[u] = b < nblk ? part[((size_t)b * nv + i) * B + c] : make_double2(0.0, 0.0);
+  }
   double sr = 0.0, si = 0.0;
-  for (int b = lane; b < nblk; b += 64) {
-    const double2 v = part[((size_t)b * nv + i) * B + c];
-    sr += v.x;
-    si += v.y;
+#pragma unroll
+  for (int u = 0; u < PL; ++u) {
+    sr += v[u].x;
+    si += v[u].y;
   }
   sr = wsum64(sr);
   si = wsum64(si);
@@ -688,12 +698,27 @@ __global__ void __launch_bounds__(256) k_arn_finish(int nblk, int B, int nv, con
   }
 }
 
-static dim3 arn_grid(int64_t rows, int B, int nblk) {
-  const int64_t need = (rows + 3) / 4;
-  return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(nblk, need)), (unsigned)((B + 63) / 64));
+static void arn_finish(int nblk, int B, int nv, const double2* part, const double* scl, double2* out, double* scl_next,
+                       int mode, hipStream_t s) {
+  const dim3 g((nv * B + 3) / 4), b(256);
+  if (nblk <= 64) hipLaunchKernelGGL(k_arn_finish<1>, g, b, 0, s, nblk, B, nv, part, scl, out, scl_next, mode);
+  else if (nblk <= 256) hipLaunchKernelGGL(k_arn_finish<4>, g, b, 0, s, nblk, B, nv, part, scl, out, scl_next, mode);
+  else hipLaunchKernelGGL(k_arn_finish<16>, g, b, 0, s, nblk, B, nv, part, scl, out, scl_next, mode);
 }
 
-int arn_blocks(int64_t rows, int B, int nblk) { return (int)arn_grid(rows, B, nblk).x; }
+// Workgroups of a column reduction over `rows` rows: as many as the rows fill with `per` rows per
+// wavefront, at most nblk. The partial sums follow the grid, so the unsplit mode keeps one (per = 1, up to
+// 64 times the rows a wavefront holds on few columns: 1024 partials where 112 hold every row).
+static dim3 arn_grid(int64_t rows, int B, int nblk, int per) {
+  const int64_t need = (rows + 4 * per - 1) / (4 * per);
+  return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(std::min(nblk, ARN_MAXBLK), need)), (unsigned)((B + 63) / 64));
+}
+// rows a wavefront takes per pass of the Gram-Schmidt kernels: two for every group of lanes (arn_lanes)
+static int arn_rows(int B) {
+  int bp = 1;
+  while (bp < B && bp < 64) bp <<= 1;
+  return 2 * (64 / bp);
+}
 
 template <int NC>
 static void spmm_arn_launch(dim3 grid, hipStream_t s, int64_t cells, int B, const int64_t* rowptr, const int32_t* col,
@@ -709,7 +734,7 @@ hipError_t launch_arnoldi_product(const ArnoldiArgs& a, const float2* t, float2*
   const int64_t rows = a.cells * a.nch;
   if (a.B >= 16 && a.nch <= 4) {
     ProfScope ps("spmm_arnoldi", s);
-    const dim3 grid = arn_grid(a.cells, a.B, a.nblk);
+    const dim3 grid = arn_grid(a.cells, a.B, a.nblk, 1);
     switch (a.nch) {
       case 1: spmm_arn_launch<1>(grid, s, a.cells, a.B, a.rowptr, a.col, a.val, a.order, t, a.V, a.vstride, a.j, a.scl, a.part); break;
       case 2: spmm_arn_launch<2>(grid, s, a.cells, a.B, a.rowptr, a.col, a.val, a.order, t, a.V, a.vstride, a.j, a.scl, a.part); break;
@@ -717,8 +742,7 @@ hipError_t launch_arnoldi_product(const ArnoldiArgs& a, const float2* t, float2*
       default: spmm_arn_launch<4>(grid, s, a.cells, a.B, a.rowptr, a.col, a.val, a.order, t, a.V, a.vstride, a.j, a.scl, a.part); break;
     }
     const int nb = (int)grid.x;
-    hipLaunchKernelGGL(k_arn_finish, dim3(((a.j + 1) * a.B + 3) / 4), dim3(256), 0, s, nb, a.B, a.j + 1, a.part, a.scl,
-                       a.H + (size_t)a.j * (a.m + 1) * a.B, nullptr, 0);
+    arn_finish(nb, a.B, a.j + 1, a.part, a.scl, a.H + (size_t)a.j * (a.m + 1) * a.B, nullptr, 0, s);
   } else {
     if (!kv_scratch) return hipErrorInvalidValue;
     {
@@ -727,14 +751,13 @@ hipError_t launch_arnoldi_product(const ArnoldiArgs& a, const float2* t, float2*
       if (e != hipSuccess) return e;
     }
     ProfScope ps("arnoldi_dots", s);
-    const dim3 grid = arn_grid(rows, a.B, a.nblk);
+    const dim3 grid = arn_grid(rows, a.B, a.nblk, a.pk.one_order ? 1 : arn_rows(a.B));
     if (a.m <= 8)
       hipLaunchKernelGGL(k_sub_dots<8>, grid, dim3(256), 0, s, rows, a.B, kv_scratch, a.V, a.vstride, a.j, a.scl, a.part);
     else
       hipLaunchKernelGGL(k_sub_dots<ARN_NV>, grid, dim3(256), 0, s, rows, a.B, kv_scratch, a.V, a.vstride, a.j, a.scl,
                          a.part);
-    hipLaunchKernelGGL(k_arn_finish, dim3(((a.j + 1) * a.B + 3) / 4), dim3(256), 0, s, (int)grid.x, a.B, a.j + 1,
-                       a.part, a.scl, a.H + (size_t)a.j * (a.m + 1) * a.B, nullptr, 0);
+    arn_finish((int)grid.x, a.B, a.j + 1, a.part, a.scl, a.H + (size_t)a.j * (a.m + 1) * a.B, nullptr, 0, s);
   }
   return hipGetLastError();
 }
@@ -742,14 +765,14 @@ hipError_t launch_arnoldi_product(const ArnoldiArgs& a, const float2* t, float2*
 hipError_t launch_arnoldi_orth(const ArnoldiArgs& a, hipStream_t s) {
   if (a.j < 0 || a.j + 1 > ARN_NV || a.j + 1 > a.m) return hipErrorInvalidValue;
   const int64_t rows = a.cells * a.nch;
-  const dim3 grid = arn_grid(rows, a.B, a.nblk);
+  const dim3 grid = arn_grid(rows, a.B, a.nblk, a.pk.one_order ? 1 : arn_rows(a.B));
   const double2* hcol = a.H + (size_t)a.j * (a.m + 1) * a.B;
   if (a.m <= 8)
     hipLaunchKernelGGL(k_orth_norm<8>, grid, dim3(256), 0, s, rows, a.B, a.V, a.vstride, a.j, hcol, a.scl, a.part);
   else
     hipLaunchKernelGGL(k_orth_norm<ARN_NV>, grid, dim3(256), 0, s, rows, a.B, a.V, a.vstride, a.j, hcol, a.scl, a.part);
-  hipLaunchKernelGGL(k_arn_finish, dim3((a.B + 3) / 4), dim3(256), 0, s, (int)grid.x, a.B, 1, a.part, a.scl,
-                     a.H + ((size_t)a.j * (a.m + 1) + a.j + 1) * a.B, a.scl + (size_t)(a.j + 1) * a.B, 1);
+  arn_finish((int)grid.x, a.B, 1, a.part, a.scl, a.H + ((size_t)a.j * (a.m + 1) + a.j + 1) * a.B,
+             a.scl + (size_t)(a.j + 1) * a.B, 1, s);
   return hipGetLastError();
 }
 
@@ -830,10 +853,11 @@ __global__ void __launch_bounds__(256) k_norm2_f64(int64_t rows, int B, const do
   arn_block_reduce(acc, dummy, 1, ln, B, part);
 }
 
-hipError_t launch_norm2_f64(int64_t rows, int B, const double2* x, double2* part, int nblk, double2* out, hipStream_t s) {
-  const dim3 grid = arn_grid(rows, B, nblk);
+hipError_t launch_norm2_f64(int64_t rows, int B, const double2* x, double2* part, int nblk, bool one_order, double2* out,
+                            hipStream_t s) {
+  const dim3 grid = arn_grid(rows, B, nblk, one_order ? 1 : arn_rows(B));
   hipLaunchKernelGGL(k_norm2_f64, grid, dim3(256), 0, s, rows, B, x, part);
-  hipLaunchKernelGGL(k_arn_finish, dim3((B + 3) / 4), dim3(256), 0, s, (int)grid.x, B, 1, part, nullptr, out, nullptr, 0);
+  arn_finish((int)grid.x, B, 1, part, nullptr, out, nullptr, 0, s);
   return hipGetLastError();
 }
 
