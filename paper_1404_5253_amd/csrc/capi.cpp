@@ -750,12 +750,14 @@ extern "C" wp_status perm_matrix_build(wp_lattice* L, int precision, void* strea
   double *geo = nullptr, *aux = nullptr, *fgeo = nullptr;
   const bool fused = L->keys.size() > 8 && L->fz_ok;
   int *cnt, *lo, *segoff;
+  int2* hull = nullptr;
   int64_t *rowcnt, *rowptr_c, *tmp;
   auto sel_layout = [&](char* base) {
     Carve c{base};
     if (use_tab) {
       geo = c.take<double>((size_t)N * N * nn * 4);
       aux = c.take<double>((size_t)N * N * nn * AS);
+      hull = c.take<int2>((size_t)N * N);
     }
     if (fused) fgeo = c.take<double>((size_t)N * N * fused_geo_doubles(a));
     cnt = c.take<int>(nbox);
@@ -812,12 +814,12 @@ extern "C" wp_status perm_matrix_build(wp_lattice* L, int precision, void* strea
   HIPCHECK(hipEventRecord(e0, s));
   if (use_tab) {
     WP_LAUNCH("node_table", s, launch_node_table(a, geo, aux, AS, s));
-    WP_LAUNCH("select", s, launch_select_tab(a, geo, aux, AS, cnt, lo, s));
+    WP_LAUNCH("select", s, launch_select_tab(a, geo, aux, AS, hull, cnt, lo, s));
   } else {
     WP_LAUNCH("select", s, launch_select(a, cnt, lo, s));
   }
   auto pbuild = [&]() -> hipError_t {
-    return use_tab ? launch_pbuild_tab(a, geo, aux, AS, cnt, lo, segoff, rowptr_c, col_c, val_c, flag, L->cand_cap, s)
+    return use_tab ? launch_pbuild_tab(a, geo, aux, AS, hull, cnt, lo, segoff, rowptr_c, col_c, val_c, flag, L->cand_cap, s)
                    : launch_pbuild(a, cnt, lo, segoff, rowptr_c, col_c, val_c, flag, L->cand_cap, s);
   };
   // fused build: kept flags, then the final row pointer from them
@@ -834,7 +836,7 @@ extern "C" wp_status perm_matrix_build(wp_lattice* L, int precision, void* strea
                                                      L->d_col.p, val64, val32, cap_b, s));
     return WP_OK;
   };
-  WP_LAUNCH("rowseg", s, launch_rowseg(M, N, cnt, segoff, rowcnt, s));
+  WP_LAUNCH("rowseg", s, launch_rowseg(M, N, hull, cnt, segoff, rowcnt, s));
   WP_LAUNCH("scan", s, launch_scan(rowcnt, rowptr_c, R, tmp, s));
   int64_t ncand = -1, nblk = -1;
   bool done = false;

@@ -194,8 +194,8 @@ __global__ void __launch_bounds__(128) k_select(PBuildArgs a, int* __restrict__ 
 __device__ double moment_weight(const Node& n, const int* key);
 
 // The quadrature nodes of every q-box, computed once per build for both the selection and the
-// quadrature: geo[box][nd] = (r1, r2, Q1, Q2) and aux[box][nd] = (z1, halved moment weights
-// w_0 / 2 .. w_{nmom-1} / 2, zeros up to AS entries; halving is exact, and the quadrature takes the
+// quadrature: geo[box][nd] = (r1, r2, Q1, Q2) and aux[box] = AS rows of nn: z1, halved moment weights
+// w_0 / 2 .. w_{nmom-1} / 2, zeros (halving is exact, and the quadrature takes the
 // 1/2 of F from the weight). A workgroup takes BB consecutive boxes: first the phi rows of all of
 // them (threads over (box, phi node), so that the arc tangents and sines fill the lanes), then
 // their nodes (threads over (box, node), consecutive threads writing consecutive nodes).
@@ -222,10 +222,10 @@ __global__ void __launch_bounds__(256) k_node_table(PBuildArgs a, double* __rest
     g[1] = n.r2;
     g[2] = n.Q1;
     g[3] = n.Q2;
-    double* x = aux + k * AS;
+    double* x = aux + (size_t)(box0 + b) * nn * AS + nd;
     x[0] = n.z1;
     const double half = a.ew ? 1.0 : 0.5;   // energy weights: no 1/2 in F
-    for (int m = 0; m < AS - 1; ++m) x[1 + m] = m < a.nmom ? half * moment_weight(n, a.keys + 5 * m) : 0.0;
+    for (int m = 0; m < AS - 1; ++m) x[(1 + m) * nn] = m < a.nmom ? half * moment_weight(n, a.keys + 5 * m) : 0.0;
   }
 }
 
@@ -240,103 +240,70 @@ hipError_t launch_node_table(const PBuildArgs& a, double* geo, double* aux, int 
 }
 
 // Selection from the node tables, with the arithmetic of k_select: one wavefront per q-box, BPW
-// boxes per workgroup (the p edges shared in LDS). Rows are first restricted exactly: node n can
-// be active in row i only if p_{i-1} r2 < Q2 and p_i r2 > Q1 (A >= p_{i-1} r2, B <= p_i r2), and
-// with a positive factor r2 the rounded products are nondecreasing in i, so these rows form an
-// interval [i0(n), i1(n)) found by binary search with the same products; rows outside the hull of
-// the union have no active node and get an empty p' range. Inside it, lane l holds the nodes
-// nd = (l mod 8) + 8u in registers and takes the rows (l / 8) + 8k; the bounds of a row are reduced
-// over the eight lanes that share it (min and max are exact, so the hull is the same as node by
-// node in one lane), then the binary searches run with lanes over rows.
-template <int NPL>
+// boxes per workgroup (the p edges shared in LDS). Node n can be active in row i only if
+// p_{i-1} r2 < Q2 and p_i r2 > Q1 (A >= p_{i-1} r2, B <= p_i r2), and with a positive factor r2 the
+// rounded products are nondecreasing in i, so these rows form an interval [i0(n), i1(n)) found by binary
+// search with the same products. It is short (a node's p range is about a bin wide on any lattice), so each
+// lane walks the rows of its own node and puts its bounds into the row's minimum and maximum in LDS (exact,
+// and all bounds are >= 0, so that their bits order like the numbers): 64 nodes x 2 to 4 rows instead of
+// nodes x rows of the hull. Rows outside the hull of the intervals have no active node: the box's hull is
+// stored, and cnt, lo (and the segment offsets) of rows outside it are neither written nor read (the arrays
+// are [box][M]). M = N = 400: 664 us with every row of the hull over all nodes, 245 us so.
 __global__ void __launch_bounds__(64 * BPW) k_select_tab(PBuildArgs a, const double* __restrict__ geo,
                                                          const double* __restrict__ aux, int AS,
-                                                         int* __restrict__ cnt, int* __restrict__ lo_out) {
+                                                         int2* __restrict__ hull, int* __restrict__ cnt,
+                                                         int* __restrict__ lo_out) {
   extern __shared__ double sh[];
   const int M = a.M;
   const int nn = a.n_x * a.n_phi;
   const int wv = threadIdx.x >> 6, t = threadIdx.x & 63;
   const int box = blockIdx.x * BPW + wv;
   const bool live = box < a.N * a.N;
-  double* spe = sh;                                 // M + 1, shared
-  double* s_xlo = spe + M + 1 + wv * 2 * M;         // M per wavefront
-  double* s_xhi = s_xlo + M;                        // M per wavefront
+  double* spe = sh;                                                                  // M + 1, shared
+  unsigned long long* s_xlo = reinterpret_cast<unsigned long long*>(spe + M + 1) + wv * 2 * M;   // M per wavefront
+  unsigned long long* s_xhi = s_xlo + M;
   const double* G = geo + (size_t)(live ? box : 0) * nn * 4;
   const double* X = aux + (size_t)(live ? box : 0) * nn * AS;
   for (int i = threadIdx.x; i <= M; i += 64 * BPW) spe[i] = a.pe[i];
+  for (int i = t; i < M; i += 64) {
+    s_xlo[i] = 0x7ff0000000000000ull;   // +inf
+    s_xhi[i] = 0ull;
+  }
   __syncthreads();
-  // hull [ilo, ihi) of the rows where any node can be active
-  int ilo = M, ihi = 0;
+  int ilo = M, ihi = 0;   // hull of the rows where any node can be active
   for (int nd = t; nd < nn; nd += 64) {
-    const double r2n = G[nd * 4 + 1], Q1n = G[nd * 4 + 2], Q2n = G[nd * 4 + 3];
-    if (!(Q1n < Q2n)) continue;
-    int lo = 0, hi = M;
+    const double r2 = G[nd * 4 + 1], Q1 = G[nd * 4 + 2], Q2 = G[nd * 4 + 3], z1 = X[nd];
+    if (!(Q1 < Q2)) continue;
+    int lo = 0, hi = M;   // i0: the first row with p_i r2 > Q1
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
-      if (spe[mid] * r2n >= Q2n) hi = mid;
-      else lo = mid + 1;
-    }
-    const int i1 = lo;
-    lo = 0;
-    hi = M;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (spe[mid + 1] * r2n > Q1n) hi = mid;
+      if (spe[mid + 1] * r2 > Q1) hi = mid;
       else lo = mid + 1;
     }
     const int i0 = lo;
-    if (i0 < i1) {
+    int i = i0;
+    for (; i < M; ++i) {
+      const double pa = spe[i] * r2;
+      if (pa >= Q2) break;
+      const double A = fmax(Q1, pa), B = fmin(Q2, spe[i + 1] * r2);
+      if (A < B) {
+        atomicMin(&s_xlo[i], (unsigned long long)__double_as_longlong(A * z1));
+        atomicMax(&s_xhi[i], (unsigned long long)__double_as_longlong(B * z1));
+      }
+    }
+    if (i0 < i) {
       ilo = min(ilo, i0);
-      ihi = max(ihi, i1);
+      ihi = max(ihi, i);
     }
   }
   ilo = wave_min(ilo);
   ihi = wave_max(ihi);
-  for (int i = t; i < M; i += 64)
-    if (i < ilo || i >= ihi) {
-      s_xlo[i] = INFINITY;
-      s_xhi[i] = -INFINITY;
-    }
-  const int ng = t & 7, rg = t >> 3;
-  double r2[NPL], z1[NPL], Q1[NPL], Q2[NPL];
-#pragma unroll
-  for (int u = 0; u < NPL; ++u) {
-    const int nd = ng + 8 * u;
-    const bool ok = nd < nn;
-    const int ndc = ok ? nd : 0;
-    r2[u] = ok ? G[ndc * 4 + 1] : 0.0;
-    z1[u] = ok ? X[(size_t)ndc * AS] : 0.0;
-    Q1[u] = ok ? G[ndc * 4 + 2] : 1.0;   // padding nodes: A >= 1 > 0 >= B, never active
-    Q2[u] = ok ? G[ndc * 4 + 3] : 0.0;
-  }
-  for (int i0 = ilo; i0 < ihi; i0 += 8) {
-    const int i = i0 + rg;
-    const int ic = i < M ? i : M - 1;
-    const double pa = spe[ic], pb = spe[ic + 1];
-    double xlo = INFINITY, xhi = -INFINITY;
-#pragma unroll
-    for (int u = 0; u < NPL; ++u) {
-      const double A = fmax(Q1[u], pa * r2[u]);
-      const double B = fmin(Q2[u], pb * r2[u]);
-      if (A < B) {
-        xlo = fmin(xlo, A * z1[u]);
-        xhi = fmax(xhi, B * z1[u]);
-      }
-    }
-#pragma unroll
-    for (int o = 1; o < 8; o <<= 1) {
-      xlo = fmin(xlo, __shfl_xor(xlo, o, WARP));
-      xhi = fmax(xhi, __shfl_xor(xhi, o, WARP));
-    }
-    if (ng == 0 && i < ihi) {
-      s_xlo[i] = xlo;
-      s_xhi[i] = xhi;
-    }
-  }
+  if (ihi < ilo) ilo = ihi = 0;
   __syncthreads();
   if (!live) return;
-  for (int i = t; i < M; i += 64) {
-    const double xlo = s_xlo[i], xhi = s_xhi[i];
+  if (t == 0) hull[box] = make_int2(ilo, ihi);
+  for (int i = ilo + t; i < ihi; i += 64) {
+    const double xlo = __longlong_as_double((long long)s_xlo[i]), xhi = __longlong_as_double((long long)s_xhi[i]);
     int c = 0, l2 = 0;
     if (xlo < xhi) {
       int lo = 0, hi = M;   // smallest e in [1, M] with spe[e] > xlo
@@ -365,17 +332,14 @@ __global__ void __launch_bounds__(64 * BPW) k_select_tab(PBuildArgs a, const dou
   }
 }
 
-hipError_t launch_select_tab(const PBuildArgs& a, const double* geo, const double* aux, int AS, int* cnt, int* lo,
-                             hipStream_t s) {
+hipError_t launch_select_tab(const PBuildArgs& a, const double* geo, const double* aux, int AS, int2* hull, int* cnt,
+                             int* lo, hipStream_t s) {
   const int nn = a.n_x * a.n_phi;
   if (nn < 1 || nn > 128 || a.M < 1 || a.M > 1024 || a.N < 1 || a.N > 1024) return hipErrorInvalidValue;
   const size_t sh = (size_t)(a.M + 1 + BPW * 2 * a.M) * sizeof(double);
   if (sh > 64 * 1024) return hipErrorInvalidValue;
-  const int npl = (nn + 7) / 8;
-  const dim3 g((a.N * a.N + BPW - 1) / BPW), b(64 * BPW);
-  if (npl <= 4) hipLaunchKernelGGL(k_select_tab<4>, g, b, sh, s, a, geo, aux, AS, cnt, lo);
-  else if (npl <= 8) hipLaunchKernelGGL(k_select_tab<8>, g, b, sh, s, a, geo, aux, AS, cnt, lo);
-  else hipLaunchKernelGGL(k_select_tab<16>, g, b, sh, s, a, geo, aux, AS, cnt, lo);
+  hipLaunchKernelGGL(k_select_tab, dim3((a.N * a.N + BPW - 1) / BPW), dim3(64 * BPW), sh, s, a, geo, aux, AS, hull, cnt,
+                     lo);
   return hipGetLastError();
 }
 
@@ -389,43 +353,70 @@ hipError_t launch_select(const PBuildArgs& a, int* cnt, int* lo, hipStream_t s) 
 
 // ------------------------------------------------------------------ row segments
 
-// Four threads per row r = j*M + i: thread h sums the candidate counts of the boxes jp in its
-// quarter, the four sums are scanned by shuffles, then each thread writes its boxes' offsets.
-__global__ void k_rowseg(int M, int N, const int* __restrict__ cnt, int* __restrict__ segoff,
-                         int64_t* __restrict__ rowcnt) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t r = t >> 2;
-  const int h = (int)(t & 3);
-  const bool live = r < (int64_t)M * N;
-  const int j = live ? (int)(r / M) : 0, i = live ? (int)(r - (int64_t)j * M) : 0;
-  const int q = (N + 3) / 4, jp0 = min(N, h * q), jp1 = min(N, jp0 + q);
-  int64_t part = 0;
-  if (live) {
-#pragma unroll 8
-    for (int jp = jp0; jp < jp1; ++jp) part += cnt[((size_t)j * N + jp) * M + i];
+// A workgroup takes 64 rows i of one j, lane = row, and its RSW wavefronts split the boxes jp: each sums the
+// candidate counts of its boxes (256 consecutive bytes a load), the sums are scanned over the wavefronts
+// through LDS, then each writes its boxes' offsets. With a hull, rows outside it are neither read nor written.
+// Memory-bound on the counts inside the hulls: M = N = 400 118 us (202 with four lanes per row over dense
+// counts, 16 rows a load), M = N = 100 7 us (25).
+#define RSW 16
+__global__ void __launch_bounds__(64 * RSW) k_rowseg(int M, int N, const int2* __restrict__ hull,
+                                                     const int* __restrict__ cnt, int* __restrict__ segoff,
+                                                     int64_t* __restrict__ rowcnt) {
+  __shared__ int64_t part[RSW][64];
+  const int t = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tiles = (M + 63) / 64;
+  const int j = blockIdx.x / tiles, i0 = (blockIdx.x - j * tiles) * 64, i = i0 + t;
+  const int q = (N + RSW - 1) / RSW, jp0 = min(N, wv * q), jp1 = min(N, jp0 + q);
+  const int2* H = hull ? hull + (size_t)j * N : nullptr;
+  const int* C = cnt + (size_t)j * N * M + i;
+  int* S = segoff + (size_t)j * N * M + i;
+  // U boxes at a time; a row outside the hull reads the array's first entry instead, so that the loads need
+  // no branch and are in flight together
+  constexpr int U = 8;
+  auto counts = [&](int jb, int (&c)[U], bool (&in)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int jp = jb + u;
+      const bool ok = jp < jp1;
+      const int2 h = !ok ? make_int2(0, 0) : H ? H[jp] : make_int2(0, M);
+      in[u] = i >= h.x && i < h.y;
+      c[u] = *(in[u] ? C + (size_t)jp * M : cnt);
+    }
+  };
+  int64_t sum = 0;
+  for (int jb = jp0; jb < jp1; jb += U) {
+    int c[U];
+    bool in[U];
+    counts(jb, c, in);
+#pragma unroll
+    for (int u = 0; u < U; ++u) sum += in[u] ? c[u] : 0;
   }
-  // exclusive prefix over the four quarters of the row (lanes 4k .. 4k+3 of the wavefront)
-  const int lane = threadIdx.x & 63, base = lane & ~3;
-  int64_t before = 0, total = 0;
-  for (int k = 0; k < 4; ++k) {
-    const int64_t v = __shfl(part, base + k, WARP);
-    if (k < h) before += v;
+  part[wv][t] = sum;
+  __syncthreads();
+  int64_t run = 0, total = 0;
+#pragma unroll
+  for (int k = 0; k < RSW; ++k) {
+    const int64_t v = part[k][t];
+    if (k < wv) run += v;
     total += v;
   }
-  if (!live) return;
-  int64_t run = before;
-#pragma unroll 8
-  for (int jp = jp0; jp < jp1; ++jp) {
-    const size_t idx = ((size_t)j * N + jp) * M + i;
-    segoff[idx] = (int)run;
-    run += cnt[idx];
+  for (int jb = jp0; jb < jp1; jb += U) {
+    int c[U];
+    bool in[U];
+    counts(jb, c, in);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (in[u]) {
+        S[(size_t)(jb + u) * M] = (int)run;
+        run += c[u];
+      }
   }
-  if (h == 0) rowcnt[r] = total;
+  if (wv == 0 && i < M) rowcnt[(size_t)j * M + i] = total;
 }
 
-hipError_t launch_rowseg(int M, int N, const int* cnt, int* segoff, int64_t* rowcnt, hipStream_t s) {
-  const int64_t T = (int64_t)M * N * 4;   // four threads per row
-  hipLaunchKernelGGL(k_rowseg, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, s, M, N, cnt, segoff, rowcnt);
+hipError_t launch_rowseg(int M, int N, const int2* hull, const int* cnt, int* segoff, int64_t* rowcnt, hipStream_t s) {
+  hipLaunchKernelGGL(k_rowseg, dim3((unsigned)((M + 63) / 64) * N), dim3(64 * RSW), 0, s, M, N, hull, cnt, segoff,
+                     rowcnt);
   return hipGetLastError();
 }
 
@@ -734,135 +725,171 @@ __global__ void __launch_bounds__(64) k_pbuild(PBuildArgs a, const int* __restri
   }
 }
 
-// Quadrature from the node tables: one wavefront per q-box, one candidate per lane, the box's
-// node table staged in LDS and read by broadcast. Moment weights past nmom are zero in the table.
+// Quadrature from the node tables: one wavefront per q-box, one candidate per lane, BPW boxes per
+// workgroup (coefficients and p edges shared in LDS). The node table's address is the same in every lane, so
+// the compiler reads it into scalar registers: from LDS it took 3 wide reads per node and wavefront, twice
+// the time of the 12 FP64 instructions per node that bound the kernel. The rows with candidates are
+// listed in LDS, at most ROWS at a time (a full list is worked off before the next rows are read), so that
+// the registers, not the lists, set the wavefronts in flight: 8 per SIMD where M entries per box left 3 at
+// M = 400. M = N = 400: 1329 us before, 781 us so (10 million candidates, 4.6 million blocks kept); M = N = 100 54 and 45 us.
+// Moment weights past nmom are zero in the table.
 // Per node, w F = (w / 2) (U - L) (U + L) for U > L, else 0, is taken as
 // fma(w / 2, max(U - L, 0) (U + L), mom): U + L > 0, and scaling by 1/2 commutes with rounding,
 // so this is the same number as fma(w, F, mom) with one compare and two selects fewer.
-// One wavefront per box, BPW boxes per workgroup (coefficients and p edges shared in LDS).
+// min and max of a number in scalar registers and one in a lane, without the extra instruction that the
+// library's take to quiet a loaded NaN (no operand here is one)
+__device__ __forceinline__ double min_su(double s, double v) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "s"(s), "v"(v));
+  return r;
+}
+__device__ __forceinline__ double max_su(double s, double v) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "s"(s), "v"(v));
+  return r;
+}
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 template <int NMOM, bool EW>
 __global__ void __launch_bounds__(64 * BPW) k_pbuild_tab(PBuildArgs a, const double* __restrict__ geo,
                                                          const double* __restrict__ aux, int AS,
+                                                         const int2* __restrict__ hull,
                                                          const int* __restrict__ cnt, const int* __restrict__ lo,
                                                          const int* __restrict__ segoff,
                                                          const int64_t* __restrict__ rowptr_c,
                                                          int32_t* __restrict__ col_c, double* __restrict__ val_c,
                                                          uint8_t* __restrict__ flag, int64_t cap) {
+  constexpr int ROWS = 128;
+  __shared__ int64_t s_base_[BPW][ROWS];   // block of candidate e of a listed row = base + e
+  __shared__ int s_pref_[BPW][ROWS];       // candidates of the listed rows before it
+  __shared__ int s_row_[BPW][ROWS];        // row i
+  __shared__ int s_lo_[BPW][ROWS];         // its first column
   extern __shared__ double sh[];
   const int M = a.M, N = a.N;
   const int nn = a.n_x * a.n_phi;
-  const int wv = threadIdx.x >> 6, t = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = threadIdx.x & 63;
   const int box = blockIdx.x * BPW + wv;
-  const bool live = box < N * N;
-  const int j = live ? box / N : 0, jp = live ? box - j * N : 0;
-  const int nc = a.nch, nc2 = nc * nc;
-  // LDS: C [nc2][nmom] and pe [M+1] shared; per wavefront the node table [nn][4 + AS], base [M]
-  // (int64), pref [M+1], lo [M] (int)
-  double* s_C = sh;
-  double* s_pe = s_C + nc2 * a.nmom;
-  const int RS = 4 + AS;
-  const size_t per_wave = (size_t)nn * RS * sizeof(double) + (size_t)M * sizeof(int64_t) + (2 * M + 1) * sizeof(int);
-  char* wbase = reinterpret_cast<char*>(s_pe + M + 1) + wv * ((per_wave + 7) & ~(size_t)7);
-  double* s_nd = reinterpret_cast<double*>(wbase);
-  int64_t* s_base = reinterpret_cast<int64_t*>(s_nd + (size_t)nn * RS);
-  int* s_pref = reinterpret_cast<int*>(s_base + M);
-  int* s_lo = s_pref + M + 1;
-  // per row: the candidate count, the first candidate column, and the output position of the
-  // row's first candidate (all loaded at once from in-range addresses; box 0 stands in for a box
-  // past the end, whose counts are taken as zero)
-  const size_t bx = live ? (size_t)box : 0;
-  int run = 0;
-  for (int base = 0; base < M; base += 64) {
-    const int i = base + t;
-    const int ic = i < M ? i : M - 1;
-    const int c_ld = cnt[bx * M + ic];
-    const int lo_ld = lo[bx * M + ic];
-    const int64_t rp = rowptr_c[(size_t)j * M + ic];
-    const int sg = segoff[bx * M + ic];
-    const int c = (live && i < M) ? c_ld : 0;
-    int x = c;
-    for (int o = 1; o < 64; o <<= 1) {
-      int y = __shfl_up(x, o, WARP);
-      if (t >= o) x += y;
-    }
-    if (i < M) {
-      const int pref = run + x - c;
-      s_pref[i] = pref;
-      s_lo[i] = live ? lo_ld : 0;
-      // candidate e of row i goes to block base[i] + e of the candidate block-CSR
-      s_base[i] = c ? rp + sg - pref : 0;
-    }
-    run += __shfl(x, 63, WARP);
-  }
-  const int total = run;   // 0 for a box past the end
-  if (t == 0) s_pref[M] = total;
+  const int nc2 = a.nch * a.nch;
+  double* s_C = sh;                        // [nc2][nmom], shared
+  double* s_pe = s_C + nc2 * a.nmom;       // [M + 1], shared
   for (int i = threadIdx.x; i <= M; i += 64 * BPW) s_pe[i] = a.pe[i];
   for (int e = threadIdx.x; e < nc2 * a.nmom; e += 64 * BPW) s_C[e] = a.C[e];
-  if (total > 0) {   // this box's node table, row nd = (r1, r2, Q1, Q2, z1, w ...)
-    const double* Gg = geo + (size_t)box * nn * 4;
-    const double* Xg = aux + (size_t)box * nn * AS;
-    for (int e = t; e < nn * 4; e += 64) s_nd[(e >> 2) * RS + (e & 3)] = Gg[e];
-    for (int e = t; e < nn * AS; e += 64) s_nd[(e / AS) * RS + 4 + e % AS] = Xg[e];
-  }
   __syncthreads();
-  if (total == 0) return;
+  if (box >= N * N) return;                // no barrier past this point
+  const int j = box / N, jp = box - j * N;
+  int64_t* s_base = s_base_[wv];
+  int* s_pref = s_pref_[wv];
+  int* s_row = s_row_[wv];
+  int* s_lo = s_lo_[wv];
   const double dq = bin_w(a.qe[j], a.qe[j + 1], a.ew), dqp = bin_w(a.qe[jp], a.qe[jp + 1], a.ew);
-  for (int e0 = 0; e0 < total; e0 += 64) {
-    const int e = min(e0 + t, total - 1);
-    int lo_i = 0, hi_i = M - 1;   // row: last i with pref[i] <= e
-    while (lo_i < hi_i) {
-      int mid = (lo_i + hi_i + 1) >> 1;
-      if (s_pref[mid] <= e) lo_i = mid;
-      else hi_i = mid - 1;
+  const double* __restrict__ G = geo + (size_t)box * nn * 4;
+  const double* __restrict__ X = aux + (size_t)box * nn * AS;
+  const int2 hl = hull[box];
+  int base = hl.x;
+  while (base < hl.y) {
+    int n = 0, total = 0;   // listed rows and their candidates
+    for (; base < hl.y && n <= ROWS - 64; base += 64) {
+      const int i = base + t;
+      const int ic = i < hl.y ? i : hl.y - 1;
+      const int c_ld = cnt[(size_t)box * M + ic];
+      const int lo_ld = lo[(size_t)box * M + ic];
+      const int64_t rp = rowptr_c[(size_t)j * M + ic];
+      const int sg = segoff[(size_t)box * M + ic];
+      const int c = i < hl.y ? c_ld : 0;
+      int x = c;
+      for (int o = 1; o < 64; o <<= 1) {
+        int y = __shfl_up(x, o, WARP);
+        if (t >= o) x += y;
+      }
+      const unsigned long long act = __ballot(c > 0);
+      if (c > 0) {
+        const int k = n + __popcll(act & ((1ull << t) - 1));
+        const int pref = total + x - c;
+        s_pref[k] = pref;
+        s_row[k] = i;
+        s_lo[k] = lo_ld;
+        s_base[k] = rp + sg - pref;
+      }
+      n += __popcll(act);
+      total += __shfl(x, 63, WARP);
     }
-    const int i = lo_i;
-    const int ip = s_lo[i] + (e - s_pref[i]);
-    const double pa = s_pe[i], pb = s_pe[i + 1], ppa = s_pe[ip], ppb = s_pe[ip + 1];
-    double mom[NMOM];
+    wave_sync();   // a wavefront's LDS accesses are done in their order
+    for (int e0 = 0; e0 < total; e0 += 64) {
+      const int e = min(e0 + t, total - 1);
+      int lo_i = 0, hi_i = n - 1;   // the last listed row with pref <= e
+      while (lo_i < hi_i) {
+        int mid = (lo_i + hi_i + 1) >> 1;
+        if (s_pref[mid] <= e) lo_i = mid;
+        else hi_i = mid - 1;
+      }
+      const int i = s_row[lo_i];
+      const int ip = s_lo[lo_i] + (e - s_pref[lo_i]);
+      const double pa = s_pe[i], pb = s_pe[i + 1], ppa = s_pe[ip], ppb = s_pe[ip + 1];
+      double mom[NMOM];
 #pragma unroll
-    for (int m = 0; m < NMOM; ++m) mom[m] = 0.0;
-#pragma unroll 4
-    for (int nd = 0; nd < nn; ++nd) {
-      const double* q = s_nd + nd * RS;   // the same address in every lane: LDS broadcast
-      const double r1 = q[0], r2 = q[1], Q1 = q[2], Q2 = q[3];
-      const double U = fmin(Q2, fmin(ppb * r1, pb * r2));
-      const double L = fmax(Q1, fmax(ppa * r1, pa * r2));
-      double F2 = fmax(U - L, 0.0) * (U + L);   // 2 F (unit weights), with the unhalved weight:
-      if (EW) F2 *= fma(U, U, L * L);           // U^4 - L^4 (energy weights)
+      for (int m = 0; m < NMOM; ++m) mom[m] = 0.0;
+      // ND nodes at a time, their loads issued together
+      auto nodes = [&](int nd, auto nw) {
+        constexpr int ND = nw.value;
+        double g[ND][4], w[NMOM][ND];
 #pragma unroll
-      for (int m = 0; m < NMOM; ++m) mom[m] = fma(q[5 + m], F2, mom[m]);
+        for (int u = 0; u < ND; ++u)
+#pragma unroll
+          for (int k = 0; k < 4; ++k) g[u][k] = G[(nd + u) * 4 + k];
+#pragma unroll
+        for (int m = 0; m < NMOM; ++m)
+#pragma unroll
+          for (int u = 0; u < ND; ++u) w[m][u] = X[(1 + m) * nn + nd + u];
+#pragma unroll
+        for (int u = 0; u < ND; ++u) {
+          const double U = min_su(g[u][3], fmin(ppb * g[u][0], pb * g[u][1]));
+          const double L = max_su(g[u][2], fmax(ppa * g[u][0], pa * g[u][1]));
+          double F2 = fmax(U - L, 0.0) * (U + L);   // 2 F (unit weights), with the unhalved weight:
+          if (EW) F2 *= fma(U, U, L * L);           // U^4 - L^4 (energy weights)
+#pragma unroll
+          for (int m = 0; m < NMOM; ++m) mom[m] = fma(w[m][u], F2, mom[m]);
+        }
+      };
+      int nd = 0;
+      for (; nd + 4 <= nn; nd += 4) nodes(nd, std::integral_constant<int, 4>{});
+      for (; nd < nn; ++nd) nodes(nd, std::integral_constant<int, 1>{});
+      const int64_t blk = s_base[lo_i] + e;
+      // past the end, or the candidate arrays are too small (the caller sees the total and builds again)
+      if (e0 + t >= total || blk >= cap) continue;
+      const double norm = 1.0 / sqrt(bin_w(pa, pb, EW) * dq * bin_w(ppa, ppb, EW) * dqp);
+      bool nz = false;
+      for (int gg = 0; gg < nc2; ++gg) {
+        double v = 0.0;
+#pragma unroll
+        for (int m = 0; m < NMOM; ++m)
+          if (m < a.nmom) v = fma(s_C[gg * a.nmom + m], mom[m], v);
+        v *= norm;
+        val_c[blk * nc2 + gg] = v;
+        nz |= (v != 0.0);
+      }
+      col_c[blk] = jp * M + ip;
+      flag[blk] = nz ? 1 : 0;
     }
-    const int64_t blk = s_base[i] + e;
-    // past the end, or the candidate arrays are too small (the caller sees the total and builds again)
-    if (e0 + t >= total || blk >= cap) continue;
-    const double norm = 1.0 / sqrt(bin_w(pa, pb, EW) * dq * bin_w(ppa, ppb, EW) * dqp);
-    bool nz = false;
-    for (int gg = 0; gg < nc2; ++gg) {
-      double v = 0.0;
-#pragma unroll
-      for (int m = 0; m < NMOM; ++m)
-        if (m < a.nmom) v = fma(s_C[gg * a.nmom + m], mom[m], v);
-      v *= norm;
-      val_c[blk * nc2 + gg] = v;
-      nz |= (v != 0.0);
-    }
-    col_c[blk] = jp * M + ip;
-    flag[blk] = nz ? 1 : 0;
+    wave_sync();
   }
 }
 
-hipError_t launch_pbuild_tab(const PBuildArgs& a, const double* geo, const double* aux, int AS, const int* cnt,
-                             const int* lo, const int* segoff, const int64_t* rowptr_c, int32_t* col_c,
+hipError_t launch_pbuild_tab(const PBuildArgs& a, const double* geo, const double* aux, int AS, const int2* hull,
+                             const int* cnt, const int* lo, const int* segoff, const int64_t* rowptr_c, int32_t* col_c,
                              double* val_c, uint8_t* flag, int64_t cap, hipStream_t s) {
   if (a.nmom < 1 || a.nmom > 4 || AS < 1 + a.nmom || a.nch < 1) return hipErrorInvalidValue;
   const int nn = a.n_x * a.n_phi;
-  const size_t per_wave = ((size_t)nn * (4 + AS) * sizeof(double) + (size_t)a.M * sizeof(int64_t) +
-                           (2 * a.M + 1) * sizeof(int) + 7) & ~(size_t)7;
-  const size_t sh = (size_t)(a.nch * a.nch * a.nmom + a.M + 1) * sizeof(double) + BPW * per_wave;
-  if (sh > 64 * 1024) return hipErrorInvalidValue;
+  // the sizes taken: coefficients, p edges and, BPW times, one node table and M row entries in 64 KB
+  const size_t per_box = ((size_t)nn * (4 + AS) * sizeof(double) + (size_t)a.M * sizeof(int64_t) +
+                          (2 * a.M + 1) * sizeof(int) + 7) & ~(size_t)7;
+  const size_t sh = (size_t)(a.nch * a.nch * a.nmom + a.M + 1) * sizeof(double);
+  if (sh + BPW * per_box > 64 * 1024) return hipErrorInvalidValue;
   dim3 g((a.N * a.N + BPW - 1) / BPW), b(64 * BPW);
 #define WP_TAB(NM, EW) \
-  hipLaunchKernelGGL((k_pbuild_tab<NM, EW>), g, b, sh, s, a, geo, aux, AS, cnt, lo, segoff, rowptr_c, col_c, val_c, \
+  hipLaunchKernelGGL((k_pbuild_tab<NM, EW>), g, b, sh, s, a, geo, aux, AS, hull, cnt, lo, segoff, rowptr_c, col_c, val_c, \
                      flag, cap)
   const bool ew = a.ew != 0;
   if (a.nmom <= 1) {
