@@ -1984,45 +1984,96 @@ __global__ void __launch_bounds__(256) k_spmm(int64_t rows, int B, int cb0, int 
   for (int g = 0; g < NC; ++g) y[((size_t)row * NC + g) * B + c] = make_x<XT, AT>(ar[g], ai[g]);
 }
 
-// LPR lanes per row (half a wavefront as launched, 256 / LPR rows per workgroup), reduction
-// within those lanes; for few columns. Rows have ~25 blocks at
-// M = N = 100, so a few lanes per row keep the lanes busy with fewer wavefronts.
-template <typename VT, typename XT, typename AT, int NC, int LPR>
+// The sums of v[0 .. V) over the 32 lanes of a half wavefront, by exchanges over lane distances O = 16 .. 1:
+// while several sums are left, each lane passes half of its own on, so that V sums take V + log2(32 / V) - 1
+// exchanges, not 5 V. Every sum is the same tree of pairs as with all lanes adding all of them. Lane hl ends
+// with the sum v[0] of index hl >> (5 - log2 V).
+template <int V, int O, typename T>
+__device__ __forceinline__ void half_sums(T* v, int hl) {
+  if constexpr (V > 1) {
+    const bool up = hl & O;
+#pragma unroll
+    for (int k = 0; k < V / 2; ++k) {
+      const T keep = up ? v[k + V / 2] : v[k], pass = up ? v[k] : v[k + V / 2];
+      v[k] = keep + __shfl_xor(pass, O, WARP);
+    }
+  } else {
+    v[0] += __shfl_xor(v[0], O, WARP);
+  }
+  if constexpr (O > 1) half_sums<(V > 1 ? V / 2 : 1), O / 2>(v, hl);
+}
+
+constexpr int pow2_up(int n) { return n <= 1 ? 1 : 2 * pow2_up((n + 1) / 2); }
+
+// For few columns: half a wavefront per row, lanes over its blocks (about 25 at M = N = 100). RT rows and CT
+// columns at a time, their loads in flight together and their sums exchanged together; a block's values are
+// read once for all CT columns. Every sum is the same for every RT and CT. Bound by the chain row pointer,
+// column, vector entry, exchange and by the gathers: 8 columns of 2 channels at M = N = 60 FP32 17 -> 12 us,
+// 4 of one channel at M = N = 400 FP64 93 -> 47 us against one column after another; loads of P0 that pass the
+// L2 by (nontemporal) made one column slower (31 -> 41 us).
+template <typename VT, typename XT, typename AT, int NC, int CT, int RT>
 __global__ void __launch_bounds__(256) k_spmv(int64_t rows, int B, int cb0, int cb1, const int64_t* __restrict__ rowptr,
                                               const int32_t* __restrict__ col, const VT* __restrict__ val,
                                               const XT* __restrict__ x, XT* __restrict__ y, const int32_t* __restrict__ order) {
-  const int64_t w = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
-  const int hl = threadIdx.x & (LPR - 1);
-  const bool live = w < rows;
-  const int64_t row = live ? (order ? order[w] : w) : 0;
-  const int64_t b0 = live ? rowptr[row] : 0, b1 = live ? rowptr[row + 1] : 0;
-  for (int c = cb0; c < cb1; ++c) {
-    AT ar[NC], ai[NC];
+  constexpr int V = 2 * NC * CT * RT, VP = pow2_up(V);
+  static_assert(VP <= 32, "one sum per lane at the end");
+  using S = decltype(XT::x);
+  const int hl = threadIdx.x & 31;
+  const int64_t w0 = ((int64_t)blockIdx.x * 8 + threadIdx.x / 32) * RT;
+  int64_t row[RT], b0[RT];
+  int len[RT], most = 0;
 #pragma unroll
-    for (int g = 0; g < NC; ++g) ar[g] = ai[g] = AT(0);
-    for (int64_t e = b0 + hl; e < b1; e += LPR) {
-      const int cc = col[e];
-      const VT* v = val + e * NC * NC;
+  for (int r = 0; r < RT; ++r) {
+    const bool live = w0 + r < rows;
+    row[r] = !live ? 0 : order ? order[w0 + r] : w0 + r;
+    b0[r] = rowptr[row[r]];
+    len[r] = live ? (int)(rowptr[row[r] + 1] - b0[r]) : 0;
+  }
 #pragma unroll
-      for (int gp = 0; gp < NC; ++gp) {
-        const XT xv = x[((size_t)cc * NC + gp) * B + c];
+  for (int r = 0; r < RT; ++r) most = max(most, len[r]);
+  for (int c0 = cb0; c0 < cb1; c0 += CT) {
+    AT acc[VP];
 #pragma unroll
-        for (int g = 0; g < NC; ++g) {
-          const AT a = (AT)v[gp * NC + g];
-          ar[g] = fma(a, (AT)xv.x, ar[g]);
-          ai[g] = fma(a, (AT)xv.y, ai[g]);
-        }
+    for (int k = 0; k < VP; ++k) acc[k] = AT(0);
+    for (int k = hl; k < most; k += 32) {
+      // a lane past the end of a row (RT > 1) reads the first block and column 0 instead and adds nothing
+      VT v[RT][NC * NC];
+      int64_t xr[RT];
+      bool in[RT];
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        in[r] = RT == 1 || k < len[r];
+        const int64_t e = in[r] ? b0[r] + k : 0;
+        const int cc = col[e];
+        xr[r] = (int64_t)(in[r] ? cc : 0) * NC * B;
+#pragma unroll
+        for (int g = 0; g < NC * NC; ++g) v[r][g] = val[e * NC * NC + g];
       }
+#pragma unroll
+      for (int gp = 0; gp < NC; ++gp)
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) {
+            const XT xv = x[xr[r] + (int64_t)gp * B + min(c0 + c, cb1 - 1)];
+            const AT xx = in[r] ? (AT)xv.x : AT(0), xy = in[r] ? (AT)xv.y : AT(0);
+#pragma unroll
+            for (int g = 0; g < NC; ++g) {
+              const AT av = in[r] ? (AT)v[r][gp * NC + g] : AT(0);
+              AT* s = acc + ((r * CT + c) * NC + g) * 2;
+              s[0] = fma(av, xx, s[0]);
+              s[1] = fma(av, xy, s[1]);
+            }
+          }
     }
+    half_sums<VP, 16>(acc, hl);
+    constexpr int DUP = 32 / VP;   // lanes with the same sum
+    const int k = hl / DUP, r = k / (2 * NC * CT), c = (k / (2 * NC)) % CT, g = (k / 2) % NC;
+    if (hl % DUP == 0 && k < V && w0 + r < rows && c0 + c < cb1) {
+      int64_t rw = row[0];
 #pragma unroll
-    for (int g = 0; g < NC; ++g) {
-      AT sr = ar[g], si = ai[g];
-#pragma unroll
-      for (int o = LPR / 2; o > 0; o >>= 1) {   // within the LPR lanes of the row
-        sr += __shfl_xor(sr, o, WARP);
-        si += __shfl_xor(si, o, WARP);
-      }
-      if (live && hl == g) y[((size_t)row * NC + g) * B + c] = make_x<XT, AT>(sr, si);
+      for (int q = 1; q < RT; ++q) rw = r == q ? row[q] : rw;
+      reinterpret_cast<S*>(y)[((rw * NC + g) * B + c0 + c) * 2 + (k & 1)] = (S)acc[0];
     }
   }
 }
@@ -2037,9 +2088,23 @@ static void spmv_dispatch(int64_t rows, int B, int cb0, int cb1, const int64_t* 
     dim3 grid((unsigned)spmv_blocks(rows, order), (cb1 - cb0 + 63) / 64);
     hipLaunchKernelGGL((k_spmm<VT, XT, AT, NC>), grid, dim3(256), 0, s, rows, B, cb0, cb1, rowptr, col, val, x, y, order);
   } else {
-    // 32 lanes per row (16 measured slower at M = N = 100)
-    hipLaunchKernelGGL((k_spmv<VT, XT, AT, NC, 32>), dim3((unsigned)((rows + 7) / 8)), dim3(256), 0, s, rows, B, cb0,
-                       cb1, rowptr, col, val, x, y, order);
+    const int nc = cb1 - cb0;
+#define WP_SPMV(CT, RT)                                                                                             \
+  hipLaunchKernelGGL((k_spmv<VT, XT, AT, NC, CT, RT>), dim3((unsigned)((rows + 8 * RT - 1) / (8 * RT))), dim3(256), \
+                     0, s, rows, B, cb0, cb1, rowptr, col, val, x, y, order)
+    // 4 columns at a time (8 of them with 2 channels: 24 us in FP64, 29 with 8 at a time, too many registers);
+    // 8 with one channel unless 4 hold the rest (8 columns 13.6 us with 4, 14.4 with 8; 15 columns 19.3 and
+    // 17.5). Two rows at a time where rows are plenty: one column of one channel at 160000 rows 31.5 -> 28.9
+    // us, at 40000 rows 11.9 -> 11.4; with 2 channels slower (28 -> 36 us at 90000 rows).
+    const bool deep = NC == 1 && rows >= 32768;
+    if (nc == 1) {
+      if (deep) {
+        if constexpr (NC == 1) WP_SPMV(1, 2);
+      } else WP_SPMV(1, 1);
+    } else if (nc == 2) WP_SPMV(2, 1);
+    else if (NC > 1 || nc <= 4 || (nc > 8 && nc <= 12)) WP_SPMV(4, 1);
+    else if constexpr (NC == 1) WP_SPMV(8, 1);
+#undef WP_SPMV
   }
 }
 
