@@ -26,6 +26,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "spmm_rows.h"
 #include "wpcd_internal.h"
 
 namespace wpcd {
@@ -1595,15 +1596,11 @@ struct FragStream {   // fragments of TPW row tiles, D steps ahead
   }
 };
 
-// Channel and column tile of a workgroup. XCD-aware order (workgroups go round robin to the 8 XCDs by
-// linear id): each XCD takes a contiguous range of the sequence (channel group, tile, channel of the
-// group), so it reads the tables of a few channels, which stay in its L2. A group holds the channels
+// Channel and column tile of a workgroup. XCD-aware order (xcd_unit) over the sequence (channel group,
+// tile, channel of the group): an XCD reads the tables of a few channels, which stay in its L2. A group holds the channels
 // whose entries of one cell share a 128-byte line of y, G1 and s; the map is a bijection over the grid.
 __device__ __forceinline__ void step_tile_of(int nch, int B, int& g, int& tile) {
-  const int ntx = gridDim.x, T = ntx * gridDim.y;
-  const int lin = blockIdx.x + ntx * blockIdx.y;
-  const int xcd = lin & 7, per = T >> 3, extra = T & 7;
-  const int idx = xcd * per + min(xcd, extra) + (lin >> 3);
+  const int ntx = gridDim.x, idx = xcd_unit(blockIdx.x + ntx * blockIdx.y, ntx * gridDim.y);
   const int cg = max(1, min(nch, 8 / B)), p = idx / (ntx * cg), rem = idx - p * ntx * cg;
   const int n = min(cg, nch - p * cg);
   tile = rem / n;
@@ -1930,58 +1927,27 @@ __device__ __forceinline__ XT make_x(AT re, AT im) {
   return v;
 }
 
-// Lanes over the columns (energies): block values and column index are wave-uniform, the
-// vector gathers are contiguous over c. For B >= 16.
-template <typename VT, typename XT, typename AT, int NC>
-__global__ void __launch_bounds__(256) k_spmm(int64_t rows, int B, int cb0, int cb1, const int64_t* __restrict__ rowptr,
-                                              const int32_t* __restrict__ col, const VT* __restrict__ val,
-                                              const XT* __restrict__ x, XT* __restrict__ y, const int32_t* __restrict__ order) {
-  const int64_t row = spmv_row(rows, order);
-  const int c = cb0 + blockIdx.y * 64 + (threadIdx.x & 63);
-  if (row < 0 || c >= cb1) return;
-  const int64_t b0 = rowptr[row], b1 = rowptr[row + 1];
-  AT ar[NC], ai[NC];
+// For B >= 16: row_product, 16 columns and 16 rows per workgroup, tile by tile of columns over all rows
+// (xcd_unit over the sequence (tile, rows)): the rows an XCD works on at a time reach the whole vector, and one
+// tile of it (2.6 MB of FP32, 5 MB of FP64 with 2 channels at M = N = 100) fits or nearly fits the XCD's 4 MB
+// L2, all 64 columns do not. Sums in block order. Bound by the gathers and, on few columns, by the chain of the
+// longest rows (185 blocks where the mean is 25). M = N = 100 in FP64, against one row and 64 columns per
+// wavefront, four blocks in flight: 2 channels, 64 columns 92 -> 52 us, 16 columns 76 -> 34; 1 channel 34 -> 29
+// and 31 -> 18.
+template <typename VT, typename E, typename AT, int NC, int U>
+__global__ void __launch_bounds__(256) k_spmm(int64_t rows, int64_t ld, int cb0, int cb1,
+                                              const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
+                                              const VT* __restrict__ val, const E* __restrict__ x, E* __restrict__ y) {
+  const int P = (int)((rows + 15) / 16);
+  const int unit = xcd_unit(blockIdx.x, gridDim.x), tile = unit / P;
+  const int64_t row = (int64_t)(unit - tile * P) * 16 + threadIdx.x / 16;
+  const int c = cb0 + tile * 16 + (threadIdx.x & 15), cl = min(c, cb1 - 1);
+  if (row >= rows) return;
+  E acc[NC];
+  row_product<NC, U, VT, AT, E>(rowptr[row], rowptr[row + 1], col, val, x + cl, ld, acc);
+  if (c < cb1)
 #pragma unroll
-  for (int g = 0; g < NC; ++g) ar[g] = ai[g] = AT(0);
-  int64_t e = b0;
-  for (; e + 4 <= b1; e += 4) {   // four blocks' gathers in flight; sums in block order
-    int cc[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) cc[u] = col[e + u];
-    XT xv[4][NC];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int gp = 0; gp < NC; ++gp) xv[u][gp] = x[((size_t)cc[u] * NC + gp) * B + c];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const VT* v = val + (e + u) * NC * NC;
-#pragma unroll
-      for (int gp = 0; gp < NC; ++gp)
-#pragma unroll
-        for (int g = 0; g < NC; ++g) {
-          const AT a = (AT)v[gp * NC + g];
-          ar[g] = fma(a, (AT)xv[u][gp].x, ar[g]);
-          ai[g] = fma(a, (AT)xv[u][gp].y, ai[g]);
-        }
-    }
-  }
-  for (; e < b1; ++e) {
-    const int cc = col[e];
-    const VT* v = val + e * NC * NC;
-#pragma unroll
-    for (int gp = 0; gp < NC; ++gp) {
-      const XT xv = x[((size_t)cc * NC + gp) * B + c];
-#pragma unroll
-      for (int g = 0; g < NC; ++g) {
-        const AT a = (AT)v[gp * NC + g];
-        ar[g] = fma(a, (AT)xv.x, ar[g]);
-        ai[g] = fma(a, (AT)xv.y, ai[g]);
-      }
-    }
-  }
-#pragma unroll
-  for (int g = 0; g < NC; ++g) y[((size_t)row * NC + g) * B + c] = make_x<XT, AT>(ar[g], ai[g]);
+    for (int g = 0; g < NC; ++g) y[(row * NC + g) * ld + c] = acc[g];
 }
 
 // The sums of v[0 .. V) over the 32 lanes of a half wavefront, by exchanges over lane distances O = 16 .. 1:
@@ -2085,8 +2051,9 @@ static void spmv_dispatch(int64_t rows, int B, int cb0, int cb1, const int64_t* 
                           const VT* val, const XT* x, XT* y, hipStream_t s, const int32_t* order) {
   // the choice depends on B only, so every launch on a given batch width sums in one order
   if (B >= 16) {
-    dim3 grid((unsigned)spmv_blocks(rows, order), (cb1 - cb0 + 63) / 64);
-    hipLaunchKernelGGL((k_spmm<VT, XT, AT, NC>), grid, dim3(256), 0, s, rows, B, cb0, cb1, rowptr, col, val, x, y, order);
+    const unsigned grid = (unsigned)((rows + 15) / 16 * ((cb1 - cb0 + 15) / 16));
+    hipLaunchKernelGGL((k_spmm<VT, XT, AT, NC, 8>), dim3(grid), dim3(256), 0, s, rows, (int64_t)B, cb0, cb1, rowptr, col,
+                       val, x, y);
   } else {
     const int nc = cb1 - cb0;
 #define WP_SPMV(CT, RT)                                                                                             \

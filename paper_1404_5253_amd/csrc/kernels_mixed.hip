@@ -4,6 +4,7 @@
 
 #include <algorithm>
 
+#include "spmm_rows.h"
 #include "wpcd_internal.h"
 
 namespace wpcd {
@@ -537,6 +538,67 @@ __global__ void __launch_bounds__(256) k_spmm_arn(int64_t cells, int B, const in
   arn_block_reduce(hr, hi, nv, ln, B, part);
 }
 
+// The same over 128-byte tiles of 16 columns, tile by tile over all rows, so that one tile of t stays in an
+// XCD's L2 (as k_spmm): row_product on 16 lanes per row, rpw rows (a multiple of 16) per workgroup, and its own
+// partial sums. With the finishing launch: M = N = 100, 2 channels, 64 columns 65 -> 52 us, 16 columns 62 -> 36;
+// M = N = 60 40 -> 28 and 37 -> 19. In the unsplit mode k_spmm_arn keeps the order of its partial sums.
+template <int NC, int NV, int U>
+__global__ void __launch_bounds__(256) k_spmm_arn_tiles(int64_t cells, int B, int P, int rpw,
+                                                        const int64_t* __restrict__ rowptr,
+                                                        const int32_t* __restrict__ col, const float* __restrict__ val,
+                                                        const float2* __restrict__ t, float2* __restrict__ V,
+                                                        int64_t vstride, int j, const double* __restrict__ scl,
+                                                        double2* __restrict__ part) {
+  constexpr int LW = 16;
+  __shared__ double2 red[4][NV][LW];
+  const int unit = xcd_unit(blockIdx.x, gridDim.x), tile = unit / P, p = unit - tile * P;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int c = tile * LW + (threadIdx.x & (LW - 1));
+  const bool live = c < B;
+  const int cl = live ? c : B - 1;
+  const float2* Vj = V + (size_t)j * vstride;
+  float2* Wo = V + (size_t)(j + 1) * vstride;
+  const float sj = (float)scl[(size_t)j * B + cl];
+  const int nv = j + 1;
+  double hr[NV], hi[NV];
+#pragma unroll
+  for (int q = 0; q < NV; ++q) hr[q] = hi[q] = 0.0;
+  const int64_t r1 = min(cells, (int64_t)(p + 1) * rpw);
+  for (int64_t row = (int64_t)p * rpw + threadIdx.x / LW; row < r1; row += 256 / LW) {
+    float2 acc[NC];
+    row_product<NC, U, float, float, float2>(rowptr[row], rowptr[row + 1], col, val, t + cl, B, acc);
+#pragma unroll
+    for (int g = 0; g < NC; ++g) {
+      const size_t idx = ((size_t)row * NC + g) * B + cl;
+      const float2 v = Vj[idx];
+      const float wr = sj * v.x - acc[g].x, wi = sj * v.y - acc[g].y;
+      if (live) Wo[idx] = make_float2(wr, wi);
+      arn_dot_row(V, vstride, nv, idx, wr, wi, hr, hi);
+    }
+  }
+  // over the row groups of the wavefront, then over the wavefronts
+#pragma unroll
+  for (int q = 0; q < NV; ++q)
+    if (q < nv) {
+      for (int o = LW; o < 64; o <<= 1) {
+        hr[q] += __shfl_xor(hr[q], o, 64);
+        hi[q] += __shfl_xor(hi[q], o, 64);
+      }
+      if (lane < LW) red[wv][q][lane] = make_double2(hr[q], hi[q]);
+    }
+  __syncthreads();
+  for (int k = threadIdx.x; k < nv * LW; k += 256) {
+    const int q = k / LW, l = k - q * LW;
+    if (tile * LW + l >= B) continue;
+    double2 s = make_double2(0.0, 0.0);
+    for (int w = 0; w < 4; ++w) {
+      s.x += red[w][q][l].x;
+      s.y += red[w][q][l].y;
+    }
+    part[((size_t)p * nv + q) * B + tile * LW + l] = s;
+  }
+}
+
 // Unfused variant (any B, any nch): w = V_j - kv with kv = P0 t from the general SpMM.
 // NV: basis slots held per lane (8 when the cycle has at most 8 Arnoldi steps, else ARN_NV): fewer
 // registers, more waves in flight for these bandwidth-bound passes.
@@ -734,14 +796,43 @@ hipError_t launch_arnoldi_product(const ArnoldiArgs& a, const float2* t, float2*
   const int64_t rows = a.cells * a.nch;
   if (a.B >= 16 && a.nch <= 4) {
     ProfScope ps("spmm_arnoldi", s);
-    const dim3 grid = arn_grid(a.cells, a.B, a.nblk, 1);
-    switch (a.nch) {
-      case 1: spmm_arn_launch<1>(grid, s, a.cells, a.B, a.rowptr, a.col, a.val, a.order, t, a.V, a.vstride, a.j, a.scl, a.part); break;
-      case 2: spmm_arn_launch<2>(grid, s, a.cells, a.B, a.rowptr, a.col, a.val, a.order, t, a.V, a.vstride, a.j, a.scl, a.part); break;
-      case 3: spmm_arn_launch<3>(grid, s, a.cells, a.B, a.rowptr, a.col, a.val, a.order, t, a.V, a.vstride, a.j, a.scl, a.part); break;
-      default: spmm_arn_launch<4>(grid, s, a.cells, a.B, a.rowptr, a.col, a.val, a.order, t, a.V, a.vstride, a.j, a.scl, a.part); break;
+    int nb;
+    if (a.pk.one_order) {
+      const dim3 grid = arn_grid(a.cells, a.B, a.nblk, 1);
+      switch (a.nch) {
+        case 1: spmm_arn_launch<1>(grid, s, a.cells, a.B, a.rowptr, a.col, a.val, a.order, t, a.V, a.vstride, a.j, a.scl, a.part); break;
+        case 2: spmm_arn_launch<2>(grid, s, a.cells, a.B, a.rowptr, a.col, a.val, a.order, t, a.V, a.vstride, a.j, a.scl, a.part); break;
+        case 3: spmm_arn_launch<3>(grid, s, a.cells, a.B, a.rowptr, a.col, a.val, a.order, t, a.V, a.vstride, a.j, a.scl, a.part); break;
+        default: spmm_arn_launch<4>(grid, s, a.cells, a.B, a.rowptr, a.col, a.val, a.order, t, a.V, a.vstride, a.j, a.scl, a.part); break;
+      }
+      nb = (int)grid.x;
+    } else {
+      // rows per workgroup: 16 on small lattices (M = N = 60 28 us, 31 with 32), else 32 (M = N = 100 52 and 59
+      // with 16), more where that leaves more partial sums than there is room for
+      const int most = std::min(a.nblk, ARN_MAXBLK);
+      int rpw = a.cells <= 4096 ? 16 : 32;
+      while ((a.cells + rpw - 1) / rpw > most) rpw += 16;
+      nb = (int)((a.cells + rpw - 1) / rpw);
+      const unsigned wgs = (unsigned)nb * ((a.B + 15) / 16);
+      // 8 blocks in flight per row while the workgroups fit the registers at once (4 per compute unit with 2
+      // channels), else 4 (2 channels, 64 columns 61 -> 52 us; 1 channel, with registers to spare, 30 and 33)
+      const bool deep = a.m <= 8 && (a.nch == 1 || wgs <= 1024);
+#define WP_TILES(NC, NV, U)                                                                                          \
+  hipLaunchKernelGGL((k_spmm_arn_tiles<NC, NV, U>), dim3(wgs), dim3(256), 0, s, a.cells, a.B, nb, rpw, a.rowptr, a.col, \
+                     a.val, t, a.V, a.vstride, a.j, a.scl, a.part)
+#define WP_TILES_NC(NC)                       \
+  if (deep) WP_TILES(NC, 8, 8);               \
+  else if (a.m <= 8) WP_TILES(NC, 8, 4);      \
+  else WP_TILES(NC, ARN_NV, 4)
+      switch (a.nch) {
+        case 1: WP_TILES_NC(1); break;
+        case 2: WP_TILES_NC(2); break;
+        case 3: WP_TILES_NC(3); break;
+        default: WP_TILES_NC(4); break;
+      }
+#undef WP_TILES_NC
+#undef WP_TILES
     }
-    const int nb = (int)grid.x;
     arn_finish(nb, a.B, a.j + 1, a.part, a.scl, a.H + (size_t)a.j * (a.m + 1) * a.B, nullptr, 0, s);
   } else {
     if (!kv_scratch) return hipErrorInvalidValue;

@@ -140,6 +140,15 @@ struct PBuildArgs {
                        // widths p_i^2 - p_{i-1}^2 in the norm (unit weights otherwise)
 };
 
+#ifdef __HIPCC__
+// Unit of work of workgroup lin of n: workgroups go round robin to the 8 XCDs by their linear id, and each
+// XCD takes a contiguous range of the units (a bijection), so that neighbouring units share one XCD's L2.
+__device__ __forceinline__ int xcd_unit(int lin, int n) {
+  const int xcd = lin & 7;
+  return xcd * (n >> 3) + min(xcd, n & 7) + (lin >> 3);
+}
+#endif
+
 // Selection (step 2): per q-box and p-row the hull [lo, lo + cnt) of possibly nonzero p' bins.
 hipError_t launch_select(const PBuildArgs& a, int* cnt, int* lo, hipStream_t s);
 // Per lattice row, offsets of each box segment and the row total (hull: the rows of each box whose cnt is
