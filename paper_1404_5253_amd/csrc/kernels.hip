@@ -1071,13 +1071,15 @@ namespace wpcd {
 // so that the logarithm keeps full relative accuracy next to its singular point.
 __device__ __forceinline__ double g1_omr2(bool pedge, double v, double PQ, double ts, double t, double base,
                                           double off, double st, double ct) {
+  const double den = pedge ? ct : st;
   if (ts < 0.0) {
-    const double r = v / (PQ * (pedge ? ct : st));
+    const double r = v / (PQ * den);
     return 1.0 - r * r;
   }
   const double d = (base - ts) + off;
   const double num = sin(d) * sin(t + ts);
-  return pedge ? -num / (ct * ct) : num / (st * st);
+  const double f = num / (den * den);
+  return pedge ? -f : f;
 }
 
 // Continuum element (1/(dp dq)) int int dp dq / (E + i0 - h p^2 - b3 q^2) (eq. dg1b, unit weights),
@@ -1101,6 +1103,7 @@ __device__ double2 g1_continuum_wave(const G1Args& g, int lane, double pa, doubl
     const double ua = E < 0.0 ? asinh(qa / kap) : qa, ub = E < 0.0 ? asinh(qb / kap) : qb;
     const double mid = 0.5 * (ua + ub);
     double part = 0.0;
+#pragma unroll 1
     for (int idx = lane; idx < 2 * g.ngl; idx += 64) {
       const int panel = idx / g.ngl, n = idx - panel * g.ngl;
       const double a = panel ? mid : ua, b = panel ? ub : mid;
@@ -1113,29 +1116,41 @@ __device__ double2 g1_continuum_wave(const G1Args& g, int lane, double pa, doubl
     re = wave_sum(part);
   } else {
     const double P = sqrt(E / h), Q = sqrt(E / b3);
-    const double t0 = atan2(qa / Q, pb / P), t1 = atan2(qb / Q, pa / P);
-    // shell crossings of the four edges (-1: none)
-    const double tpa = pa / P < 1.0 ? acos(pa / P) : -1.0, tpb = pb / P < 1.0 ? acos(pb / P) : -1.0;
-    const double tqa = qa / Q < 1.0 ? asin(qa / Q) : -1.0, tqb = qb / Q < 1.0 ? asin(qb / Q) : -1.0;
-    double pts[8];
-    int np = 0;
-    pts[np++] = t0;
-    pts[np++] = t1;
-    const double cand[6] = {atan2(qa / Q, pa / P), atan2(qb / Q, pb / P), tpa, tpb, tqa, tqb};
-    for (int c = 0; c < 6; ++c)
-      if (cand[c] > t0 && cand[c] < t1) pts[np++] = cand[c];
-    for (int x = 1; x < np; ++x)  // insertion sort (np <= 8)
-      for (int y = x; y > 0 && pts[y - 1] > pts[y]; --y) {
-        double tmp = pts[y];
-        pts[y] = pts[y - 1];
-        pts[y - 1] = tmp;
-      }
+    // The panel ends, one per lane (lanes 0 .. 7): t0, t1, the two other corners, and the shell crossings of
+    // the four edges (-1: none). Every lane evaluating all of them took as long as the nodes.
+    const double cpa = pa / P, cpb = pb / P, cqa = qa / Q, cqb = qb / Q;
+    const int l8 = lane & 7;
+    double pt;
+    if (l8 < 4) {
+      pt = atan2((l8 & 1) ? cqb : cqa, l8 == 0 || l8 == 3 ? cpb : cpa);
+    } else {
+      const double c = l8 == 4 ? cpa : l8 == 5 ? cpb : l8 == 6 ? cqa : cqb;
+      pt = c < 1.0 ? (l8 < 6 ? acos(c) : asin(c)) : -1.0;
+    }
+    const double t0 = __shfl(pt, 0, WARP), t1 = __shfl(pt, 1, WARP);
+    const double tpa = __shfl(pt, 4, WARP), tpb = __shfl(pt, 5, WARP), tqa = __shfl(pt, 6, WARP), tqb = __shfl(pt, 7, WARP);
+    // sorted: the point of rank r moves to lane r
+    const bool use = lane < 2 || (lane < 8 && pt > t0 && pt < t1);
+    const int np = __popcll(__ballot(use));
+    int rank = 0;
+    for (int m = 0; m < 8; ++m) {
+      const double o = __shfl(pt, m, WARP);
+      const bool uo = m < 2 || (o > t0 && o < t1);
+      rank += uo && (o < pt || (o == pt && m < lane));
+    }
+    if (!use) rank = lane < 8 ? 8 + lane : lane;   // lanes past 7 are not read
+    const long long bits = __double_as_longlong(pt);
+    const int slo = __builtin_amdgcn_ds_permute(rank << 2, (int)bits);
+    const int shi = __builtin_amdgcn_ds_permute(rank << 2, (int)(bits >> 32));
+    const double sorted = __longlong_as_double(((long long)shi << 32) | (unsigned)slo);
     double part = 0.0;
     const int total = (np - 1) * g.nts;
-    for (int idx = lane; idx < total; idx += 64) {
+#pragma unroll 1
+    for (int i0 = 0; i0 < total; i0 += 64) {
+      const int idx = min(i0 + lane, total - 1);
       const int sgi = idx / g.nts, n = idx - sgi * g.nts;
-      const double a = pts[sgi], b = pts[sgi + 1];
-      if (!(b > a)) continue;
+      const double a = __shfl(sorted, sgi, WARP), b = __shfl(sorted, sgi + 1, WARP);
+      if (i0 + lane >= total || !(b > a)) continue;
       const double u = g.ts_u[n];
       // node placed from the nearer end: t = base + off
       const double base = (u <= 0.5) ? a : b;
@@ -1159,20 +1174,21 @@ __device__ double2 g1_continuum_wave(const G1Args& g, int lane, double pa, doubl
       const bool hp = rp <= rq;
       const double rhi = hp ? rp : rq;
       if (rhi > rlo) {
-        const double xh = hp ? g1_omr2(true, pb, P, tpb, t, base, off, st, ct)
-                             : g1_omr2(false, qb, Q, tqb, t, base, off, st, ct);
+        // the lanes' edges differ: chosen before the one evaluation, not by a branch around two
+        const double xh = g1_omr2(hp, hp ? pb : qb, hp ? P : Q, hp ? tpb : tqb, t, base, off, st, ct);
         double f = -0.5 * log(fabs(xh));
         if (elo >= 0) {
-          const double xl = elo == 0 ? g1_omr2(true, pa, P, tpa, t, base, off, st, ct)
-                                     : g1_omr2(false, qa, Q, tqa, t, base, off, st, ct);
+          const bool lp = elo == 0;
+          const double xl = g1_omr2(lp, lp ? pa : qa, lp ? P : Q, lp ? tpa : tqa, t, base, off, st, ct);
           f += 0.5 * log(fabs(xl));
         }
         if (isfinite(f)) part += 0.5 * (b - a) * g.ts_w[n] * f;   // a node on the shell carries no weight
       }
     }
     re = wave_sum(part) / sqrt(h * b3);
-    const double lo_p = acos(fmin(1.0, pb / P)), hi_p = acos(fmin(1.0, pa / P));
-    const double lo_q = asin(fmin(1.0, qa / Q)), hi_q = asin(fmin(1.0, qb / Q));
+    // acos and asin of min(1, .): the crossings, or acos(1) and asin(1)
+    const double lo_p = fmax(0.0, tpb), hi_p = fmax(0.0, tpa);
+    const double lo_q = tqa >= 0.0 ? tqa : M_PI / 2, hi_q = tqb >= 0.0 ? tqb : M_PI / 2;
     im = -M_PI / (2.0 * sqrt(h * b3)) * fmax(0.0, fmin(hi_p, hi_q) - fmax(lo_p, lo_q));
   }
   const double d = (pb - pa) * (qb - qa);
@@ -1195,6 +1211,16 @@ struct G1Elem {
 };
 __device__ __forceinline__ G1Elem g1_decode(const G1Args& g, int64_t el) {
   G1Elem d;
+  if ((el >> 32) == 0) {   // 32-bit divisions are several times cheaper
+    unsigned r = (unsigned)el;
+    d.e = (int)(r % (unsigned)g.nE);
+    r /= (unsigned)g.nE;
+    d.j = (int)(r % (unsigned)g.N);
+    r /= (unsigned)g.N;
+    d.k = (int)(r % (unsigned)g.M);
+    d.w = (int)(r / (unsigned)g.M);
+    return d;
+  }
   d.e = (int)(el % g.nE);
   int64_t r = el / g.nE;
   d.j = (int)(r % g.N);
@@ -1258,13 +1284,8 @@ __device__ bool g1_continuum_lane(const G1Args& g, int sub, double pa, double pb
   } else {
     return false;
   }
-  // rho = |x + sqrt(x^2 - 1)| on the branch with modulus > 1
-  const double ar = xr * xr - xi * xi - 1.0, ai = 2.0 * xr * xi;
-  const double mod = sqrt(sqrt(ar * ar + ai * ai));
-  const double ang = 0.5 * atan2(ai, ar);
-  const double sr = mod * cos(ang), si = mod * sin(ang);
-  const double r1 = hypot(xr + sr, xi + si), r2 = hypot(xr - sr, xi - si);
-  if (fmax(r1, r2) < 3.0) return false;
+  // rho + 1 / rho = |x - 1| + |x + 1| (the sum of the distances to the foci of the ellipse through x), >= 3 + 1/3
+  if (sqrt((xr - 1.0) * (xr - 1.0) + xi * xi) + sqrt((xr + 1.0) * (xr + 1.0) + xi * xi) < 10.0 / 3.0) return false;
   const double sh = sqrt(h);
   double acc = 0.0;
 #pragma unroll
@@ -1279,7 +1300,8 @@ __device__ bool g1_continuum_lane(const G1Args& g, int sub, double pa, double pb
   return true;
 }
 
-// One lane per element: bound-continuum elements and the continuum elements the lane rule
+// Four lanes per element (64 energies, 2 waves, M = N = 100: 227 -> 195 us with rho by the foci and 32-bit
+// divisions): bound-continuum elements and the continuum elements the lane rule
 // accepts are written; the others are appended to a work list for k_g1_wave.
 __global__ void __launch_bounds__(256) k_g1_lane(G1Args g) {
   const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1313,7 +1335,9 @@ __global__ void __launch_bounds__(256) k_g1_lane(G1Args g) {
   }
 }
 
-// One wavefront per deferred element (the boxes the energy shell crosses or passes close to).
+// One wavefront per deferred element (the boxes the energy shell crosses or passes close to). Bound by the FP64
+// functions of a node and, before the panel ends were shared out over the lanes, by those as much: 64 energies,
+// 2 waves, M = N = 100 281 -> 143 us, one energy 42 -> 20.
 __global__ void __launch_bounds__(256) k_g1_wave(G1Args g) {
   const int lane = threadIdx.x & 63;
   const int cnt = *g.wl_n;
