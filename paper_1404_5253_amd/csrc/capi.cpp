@@ -1035,50 +1035,32 @@ static wp_status solve_fp64(wp_lattice* L, const std::vector<double>& Elab, cons
   wp_lattice::Solve64WS own_ws;
   wp_lattice::Solve64WS& ws = ws_lock.owns_lock() ? L->ws64 : own_ws;
   StreamDrain drain{s};   // idle stream before the workspace is released or handed on
-  DBuf<double2>&dG = ws.dG, &dy = ws.dy, &ds = ws.ds, &dacap = ws.dacap;
-  DBuf<int>&dj0 = ws.dj0, &dg0 = ws.dg0, &dfin = ws.dfin;
-  DBuf<double>& dE = ws.dE;
+  DBuf<double2>&dG = ws.dG, &dy = ws.dy, &ds = ws.ds;
   DBuf<int64_t>& g1w = ws.g1w;
   DevAlloc* al = &L->al;
-  if (!g1_work(L, nE, g1w)) return fail(WP_ENOMEM, "device allocation (G1 work list)");
-  if (!grow(dG, al, D * B) || !grow(dy, al, D * B) || !grow(ds, al, D * B) ||
-      !grow(dacap, al, (size_t)2 * chunk * B * nfin) || !grow(dj0, al, B) || !grow(dg0, al, B) ||
-      !grow(dfin, al, nfin) || !grow(dE, al, nE))
-    return fail(WP_ENOMEM, "device allocation (solve vectors)");
-  HIPCHECK(hipMemcpyAsync(dE.p, Etot.data(), nE * sizeof(double), hipMemcpyHostToDevice, s));
-  WP_LAUNCH("g1", s, launch_g1(g1_args(L, dE.p, nE, nfin, 0, B, dG.p, g1w.p), s));
-  HIPCHECK(hipMemcpyAsync(dj0.p, j0.data(), B * sizeof(int), hipMemcpyHostToDevice, s));
-  HIPCHECK(hipMemcpyAsync(dg0.p, g0.data(), B * sizeof(int), hipMemcpyHostToDevice, s));
-  HIPCHECK(hipMemcpyAsync(dfin.p, L->opens.data(), nfin * sizeof(int), hipMemcpyHostToDevice, s));
-  const double* val = L->d_val64.p;
-  if (!val) return fail(WP_ENOTREADY, "FP64 solve needs P0 built with WP_P_FP64");
-  HIPCHECK(launch_init_rhs64(M, N, nch, B, L->d_W.p, L->d_wave.p, dj0.p, dg0.p, ds.p, s));
-  HIPCHECK(launch_spmv_f64(R, nch, B, L->d_rowptr.p, L->d_col.p, val, ds.p, dy.p, s, 0, -1, order, pk_view(L, o.spmm_cols)));
-  std::vector<ColState> cs(B);
-  for (auto& c : cs) {
-    c.w.resize(nfin);
-    c.S.assign(nfin, cplx(0, 0));
-  }
-  // Chunks of `chunk` iterations; the captured terms of a chunk go to pinned host memory. For
+  // Chunks of `chunk` iterations; the terms are captured straight into pinned host memory. For
   // small batches (iterations of a few microseconds) chunk k + 1 is enqueued before chunk k is
   // read, so the device does not wait for the Pade check, at the price of at most one chunk
-  // past convergence; large batches read each chunk before the next is enqueued.
+  // past convergence; large batches read each chunk before the next is enqueued, two terms at a time
+  // while the rest of it runs (64 energies at M = N = 100: about 300 us a chunk on the host).
   const size_t per_chunk = (size_t)chunk * B * nfin;
+  // energies, then on-shell bins, initial channels and finals: staged behind the captured terms, one copy
+  const size_t n_in = nE + (size_t)(2 * B + nfin + 1) / 2, pin_n = 2 * per_chunk + (n_in + 1) / 2;
   const bool overlap = D * B <= ((int64_t)1 << 20);
   std::unique_lock<std::mutex> pin_lock(L->pin_mu, std::try_to_lock);
   double2* own = nullptr;
   double2* pin = nullptr;
   if (pin_lock.owns_lock()) {
-    if (L->pin_cap < 2 * per_chunk) {
+    if (L->pin_cap < pin_n) {
       if (L->pin) (void)hipHostFree(L->pin);
       L->pin = nullptr;
       L->pin_cap = 0;
-      HIPCHECK(hipHostMalloc((void**)&L->pin, 2 * per_chunk * sizeof(double2), hipHostMallocDefault));
-      L->pin_cap = 2 * per_chunk;
+      HIPCHECK(hipHostMalloc((void**)&L->pin, pin_n * sizeof(double2), hipHostMallocDefault));
+      L->pin_cap = pin_n;
     }
     pin = L->pin;
   } else {   // another call on this lattice holds the shared buffer
-    HIPCHECK(hipHostMalloc((void**)&own, 2 * per_chunk * sizeof(double2), hipHostMallocDefault));
+    HIPCHECK(hipHostMalloc((void**)&own, pin_n * sizeof(double2), hipHostMallocDefault));
     pin = own;
   }
   struct PinGuard {   // the stream drains before the staging buffer is released (also on errors)
@@ -1089,16 +1071,41 @@ static wp_status solve_fp64(wp_lattice* L, const std::vector<double>& Elab, cons
       if (own) (void)hipHostFree(own);
     }
   } pin_guard{own, s};
-  hipEvent_t ev[2];
-  HIPCHECK(hipEventCreateWithFlags(&ev[0], hipEventDisableTiming));
-  HIPCHECK(hipEventCreateWithFlags(&ev[1], hipEventDisableTiming));
+  if (!g1_work(L, nE, g1w)) return fail(WP_ENOMEM, "device allocation (G1 work list)");
+  if (!grow(dG, al, D * B) || !grow(dy, al, D * B) || !grow(ds, al, D * B) || !grow(ws.din, al, n_in))
+    return fail(WP_ENOMEM, "device allocation (solve vectors)");
+  double* h_in = reinterpret_cast<double*>(pin + 2 * per_chunk);
+  int* h_idx = reinterpret_cast<int*>(h_in + nE);
+  std::copy(Etot.begin(), Etot.end(), h_in);
+  std::copy(j0.begin(), j0.end(), h_idx);
+  std::copy(g0.begin(), g0.end(), h_idx + B);
+  std::copy(L->opens.begin(), L->opens.end(), h_idx + 2 * B);
+  HIPCHECK(hipMemcpyAsync(ws.din.p, h_in, n_in * sizeof(double), hipMemcpyHostToDevice, s));
+  const double* dE = ws.din.p;
+  const int* dj0 = reinterpret_cast<const int*>(ws.din.p + nE);
+  const int *dg0 = dj0 + B, *dfin = dj0 + 2 * B;
+  WP_LAUNCH("g1", s, launch_g1(g1_args(L, dE, nE, nfin, 0, B, dG.p, g1w.p), s));
+  const double* val = L->d_val64.p;
+  if (!val) return fail(WP_ENOTREADY, "FP64 solve needs P0 built with WP_P_FP64");
+  HIPCHECK(launch_init_rhs64(M, N, nch, B, L->d_W.p, L->d_wave.p, dj0, dg0, ds.p, s));
+  HIPCHECK(launch_spmv_f64(R, nch, B, L->d_rowptr.p, L->d_col.p, val, ds.p, dy.p, s, 0, -1, order, pk_view(L, o.spmm_cols)));
+  std::vector<ColState> cs(B);
+  for (auto& c : cs) {
+    c.w.resize(nfin);
+    c.S.assign(nfin, cplx(0, 0));
+  }
+  // ev[slot]: the end of a chunk; part[q]: two more terms of the running chunk captured
+  hipEvent_t ev[2] = {nullptr, nullptr}, part[chunk / 2] = {};
   struct EvGuard {
-    hipEvent_t* e;
+    hipEvent_t *e, *p;
     ~EvGuard() {
-      (void)hipEventDestroy(e[0]);
-      (void)hipEventDestroy(e[1]);
+      for (int k = 0; k < 2; ++k)
+        if (e[k]) (void)hipEventDestroy(e[k]);
+      for (int k = 0; k < chunk / 2; ++k)
+        if (p[k]) (void)hipEventDestroy(p[k]);
     }
-  } ev_guard{ev};
+  } ev_guard{ev, part};
+  for (auto& x : ev) HIPCHECK(hipEventCreateWithFlags(&x, hipEventDisableTiming));
   int launched = 0;   // iterations enqueued
   int T_of[2] = {0, 0};
   // Terms still needed by the slowest unfinished column after the chunks read so far, predicted
@@ -1112,11 +1119,14 @@ static wp_status solve_fp64(wp_lattice* L, const std::vector<double>& Elab, cons
     if (need < 0) return chunk;
     return std::max(2, std::min(chunk, need - in_flight + 1));
   };
-  // T terms into capture slot `slot` (rows slot * chunk + t of dacap), then their copy to the
-  // slot's pinned staging
+  const bool use_graph = o.graph == 1 && !profiling_enabled();
+  const bool parts = !overlap && !use_graph;
+  if (parts)
+    for (auto& x : part) HIPCHECK(hipEventCreateWithFlags(&x, hipEventDisableTiming));
+  // T terms into capture slot `slot` (rows slot * chunk + t of pin)
   auto record_chunk = [&](hipStream_t st, int slot, int T) -> hipError_t {
     for (int t = 0; t < T; ++t) {
-      RotArgs ro{M, N, nch, B, L->d_O.p, L->d_wave.p, dG.p, dacap.p, dj0.p, dfin.p, nfin,
+      RotArgs ro{M, N, nch, B, L->d_O.p, L->d_wave.p, dG.p, pin, dj0, dfin, nfin,
                  (int64_t)(slot * chunk + t) * B * nfin};
       ro.tile = o.step_tile;
       ro.Of = L->d_Of.p;
@@ -1127,6 +1137,7 @@ static wp_status solve_fp64(wp_lattice* L, const std::vector<double>& Elab, cons
         e = launch_step64(ro, L->d_W.p, dy.p, ds.p, st);
       }
       if (e != hipSuccess) return e;
+      if (parts && ((t & 1) || t == T - 1) && (e = hipEventRecord(part[t / 2], st)) != hipSuccess) return e;
       {
         ProfScope ps("spmv64", st);
         e = launch_spmv_f64(R, nch, B, L->d_rowptr.p, L->d_col.p, val, ds.p, dy.p, st, 0, -1, order,
@@ -1134,17 +1145,14 @@ static wp_status solve_fp64(wp_lattice* L, const std::vector<double>& Elab, cons
       }
       if (e != hipSuccess) return e;
     }
-    return hipMemcpyAsync(pin + slot * per_chunk, dacap.p + (size_t)slot * per_chunk,
-                          (size_t)T * B * nfin * sizeof(double2), hipMemcpyDeviceToHost, st);
+    return hipSuccess;
   };
-  // full chunks replayed from a graph (o.graph), kept by the work space between calls
-  const bool use_graph = o.graph == 1 && !profiling_enabled();
+  // full chunks replayed from a graph (use_graph), kept by the work space between calls
   auto enqueue = [&](int slot, int want) -> wp_status {
     const int T = std::min(want, max_iter - launched);
     if (use_graph && T == chunk) {
       const std::vector<int64_t> key{slot, M, N, nch, B, nfin, chunk, o.step_tile, o.spmm_cols,
-                                     (int64_t)dG.p, (int64_t)dy.p, (int64_t)ds.p, (int64_t)dacap.p, (int64_t)dj0.p,
-                                     (int64_t)dfin.p, (int64_t)pin, (int64_t)L->d_O.p, (int64_t)L->d_W.p,
+                                     (int64_t)dG.p, (int64_t)dy.p, (int64_t)ds.p, (int64_t)dj0, (int64_t)pin, (int64_t)L->d_O.p, (int64_t)L->d_W.p,
                                      (int64_t)L->d_wave.p, (int64_t)L->d_rowptr.p, (int64_t)L->d_col.p,
                                      (int64_t)val, (int64_t)order, (int64_t)L->d_pkt.p, L->blocks};
       HIPCHECK(graph_run(L, ws.chunk_graph[slot], key, s, [&](hipStream_t st) { return record_chunk(st, slot, T); }));
@@ -1176,20 +1184,23 @@ static wp_status solve_fp64(wp_lattice* L, const std::vector<double>& Elab, cons
       cur = k & 1;
       if (wp_status st1 = enqueue(cur, chunk)) return st1;
     }
-    HIPCHECK(hipEventSynchronize(ev[cur]));
     const double2* hcap = pin + cur * per_chunk;
-    bool all_done = true;
-    for (int c = 0; c < B; ++c) {
-      for (int t = 0; t < T_of[cur] && !cs[c].done; ++t) {
-        std::vector<cplx> a(nfin);
-        for (int f = 0; f < nfin; ++f) {
-          double2 v = hcap[((size_t)t * B + c) * nfin + f];
-          a[f] = cplx(v.x, v.y);
+    std::vector<cplx> a(nfin);
+    for (int t0 = 0; t0 < T_of[cur];) {   // the terms captured so far
+      const int t1 = parts ? std::min(t0 + 2, T_of[cur]) : T_of[cur];
+      HIPCHECK(hipEventSynchronize(parts ? part[t0 / 2] : ev[cur]));
+      for (int c = 0; c < B; ++c)
+        for (int t = t0; t < t1 && !cs[c].done; ++t) {
+          for (int f = 0; f < nfin; ++f) {
+            double2 v = hcap[((size_t)t * B + c) * nfin + f];
+            a[f] = cplx(v.x, v.y);
+          }
+          column_push(cs[c], a.data(), nfin, o.tol, o.accept);
         }
-        column_push(cs[c], a.data(), nfin, o.tol, o.accept);
-      }
-      all_done &= cs[c].done;
+      t0 = t1;
     }
+    bool all_done = true;
+    for (int c = 0; c < B; ++c) all_done &= cs[c].done;
     need = 0;
     for (int c = 0; c < B && need >= 0; ++c) {
       const ColState& q = cs[c];

@@ -952,6 +952,22 @@ hipError_t launch_norm2_f64(int64_t rows, int B, const double2* x, double2* part
   return hipGetLastError();
 }
 
+__global__ void k_export_cycle(int B, int nH, int nS, const double2* __restrict__ nrm, const double2* __restrict__ H,
+                               const double* __restrict__ scl, double2* __restrict__ hn, double2* __restrict__ hH,
+                               double* __restrict__ hsc) {
+  int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < B) hn[t] = nrm[t];
+  if (t < nH) hH[t] = H[t];
+  if (t < nS) hsc[t] = scl[t];
+}
+hipError_t launch_export_cycle(int B, int m, const double2* nrm, const double2* H, const double* scl, double2* hn,
+                               double2* hH, double* hsc, hipStream_t s) {
+  const int nH = m * (m + 1) * B, nS = (m + 1) * B;   // m >= 1: the Hessenberg entries are the most
+  hipLaunchKernelGGL(k_export_cycle, dim3((std::max(nH, nS) + 255) / 256), dim3(256), 0, s, B, nH, nS, nrm, H, scl, hn,
+                     hH, hsc);
+  return hipGetLastError();
+}
+
 // out[d][c] = x[d][c] / sqrt(nrm2[c]) with x in FP64, out in FP32
 __global__ void k_scale_d2f(int64_t n, int B, const double2* __restrict__ nrm2, const double2* __restrict__ x,
                             float2* __restrict__ out, double* __restrict__ scl0) {

@@ -91,17 +91,19 @@ wp_status wpcd::MixedWork::make(wp_lattice* Lp, int B_, int m_, bool split_) {
   // grow-only, so that a work object kept by the lattice is reused by later calls
   DevAlloc* al = &L->al;
   if (!grow(dG64, al, DB) || !grow(db, al, DB) || !grow(dy, al, DB) || !grow(dr, al, DB) || !grow(dKy, al, DB) ||
-      !grow(ds64, al, DB) || !grow(dcap, al, (size_t)B * nfin) || !grow(dcoef, al, (size_t)(m + 1) * B) ||
+      !grow(ds64, al, DB) || !grow(dcoef, al, (size_t)(m + 1) * B) ||
       !grow(H, al, (size_t)m * (m + 1) * B) || !grow(part, al, (size_t)kNblk * ARN_NV * B) || !grow(nrm, al, B) ||
       !grow(dG32, al, DB) || !grow(V, al, (size_t)(m + 1) * DB) || !grow(t32, al, DB) ||
       (!fused && !grow(kv32, al, DB)) || !grow(scl, al, (size_t)(m + 1) * B) || !grow(dj0, al, B) ||
       !grow(dfin, al, nfin))
     return fail(WP_ENOMEM, "device allocation (mixed solve)");
-  hc.resize((size_t)B * nfin);
-  hH.resize((size_t)m * (m + 1) * B);
-  hn.resize(B);
-  hsc.resize((size_t)(m + 1) * B);
-  coef.resize((size_t)(m + 1) * B);
+  const size_t nH = (size_t)m * (m + 1) * B, nV = (size_t)(m + 1) * B;
+  if (!pin.grow(B + nH + nV + (size_t)B * nfin + (nV + 1) / 2)) return fail(WP_ENOMEM, "pinned host memory (mixed solve)");
+  hn = pin.p;
+  hH = hn + B;
+  coef = hH + nH;
+  hc = coef + nV;
+  hsc = reinterpret_cast<double*>(hc + (size_t)B * nfin);
   return WP_OK;
 }
 
@@ -176,11 +178,9 @@ wp_status wpcd::mixed_cycle(MixedWork& w, hipStream_t s, bool y_is_zero, const s
   } else {
     HIPCHECK(record_sweep(s));
   }
-  HIPCHECK(hipMemcpyAsync(w.hn.data(), w.nrm.p, B * sizeof(double2), hipMemcpyDeviceToHost, s));
-  HIPCHECK(hipMemcpyAsync(w.hH.data(), w.H.p, w.hH.size() * sizeof(double2), hipMemcpyDeviceToHost, s));
-  HIPCHECK(hipMemcpyAsync(w.hsc.data(), w.scl.p, w.hsc.size() * sizeof(double), hipMemcpyDeviceToHost, s));
+  HIPCHECK(launch_export_cycle(B, m, w.nrm.p, w.H.p, w.scl.p, w.hn, w.hH, w.hsc, s));
   HIPCHECK(hipStreamSynchronize(s));
-  std::fill(w.coef.begin(), w.coef.end(), make_double2(0.0, 0.0));
+  std::fill(w.coef, w.coef + (size_t)(m + 1) * B, make_double2(0.0, 0.0));
   std::vector<cplx> Hc((size_t)m * (m + 1));
   for (int c = 0; c < B; ++c) {
     if (!active[c]) continue;
@@ -196,11 +196,10 @@ wp_status wpcd::mixed_cycle(MixedWork& w, hipStream_t s, bool y_is_zero, const s
       w.coef[(size_t)i * B + c] = make_double2(v.real(), v.imag());
     }
   }
-  HIPCHECK(hipMemcpyAsync(w.dcoef.p, w.coef.data(), w.coef.size() * sizeof(double2), hipMemcpyHostToDevice, s));
+  HIPCHECK(hipMemcpyAsync(w.dcoef.p, w.coef, (size_t)(m + 1) * B * sizeof(double2), hipMemcpyHostToDevice, s));
   WP_LAUNCH("lincomb", s, launch_lincomb(D, B, m, w.V.p, DB, w.dcoef.p, w.dy.p, s));
   WP_LAUNCH("capture", s,
-            launch_capture64(M, nch, B, nfin, L->d_O.p, L->d_wave.p, w.dj0.p, w.dfin.p, w.dy.p, w.dcap.p, s));
-  HIPCHECK(hipMemcpyAsync(w.hc.data(), w.dcap.p, w.hc.size() * sizeof(double2), hipMemcpyDeviceToHost, s));
+            launch_capture64(M, nch, B, nfin, L->d_O.p, L->d_wave.p, w.dj0.p, w.dfin.p, w.dy.p, w.hc, s));
   HIPCHECK(hipStreamSynchronize(s));
   return WP_OK;
 }

@@ -364,6 +364,9 @@ hipError_t launch_arnoldi_orth(const ArnoldiArgs& a, hipStream_t s);
 // U[c][f] = e0^T O y at (g = finals[f], j = j0[c], k = 0), FP64
 hipError_t launch_capture64(int M, int nch, int B, int nfin, const double* O, const int* wave, const int* j0,
                             const int* finals, const double2* y, double2* out, hipStream_t s);
+// norms [B], Hessenberg columns [m][m + 1][B] and scales [m + 1][B] of a cycle into (pinned) host memory
+hipError_t launch_export_cycle(int B, int m, const double2* nrm, const double2* H, const double* scl, double2* hn,
+                               double2* hH, double* hsc, hipStream_t s);
 // out[t] = (O y) of cell t = (column c, channel g, pseudostate k, q bin j), n cells
 hipError_t launch_project_cells(int M, int nch, int B, const double* O, const int* wave, const int4* cells, int n,
                                 const double2* y, double2* out, hipStream_t s);

@@ -36,6 +36,31 @@ using namespace wpcd;
     if (e_ != hipSuccess) return wpcd::fail(WP_EDEVICE, std::string(#expr) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
+// Pinned host memory, grow-only; device kernels write it and copies to the device read it.
+struct PinBuf {
+  double2* p = nullptr;
+  size_t n = 0;
+  bool grow(size_t k) {
+    if (n >= k) return true;
+    reset();
+    if (hipHostMalloc((void**)&p, k * sizeof(double2), hipHostMallocDefault) != hipSuccess) {
+      p = nullptr;
+      return false;
+    }
+    n = k;
+    return true;
+  }
+  void reset() {
+    if (p) (void)hipHostFree(p);
+    p = nullptr;
+    n = 0;
+  }
+  PinBuf() = default;
+  PinBuf(const PinBuf&) = delete;
+  PinBuf& operator=(const PinBuf&) = delete;
+  ~PinBuf() { reset(); }
+};
+
 struct PairWave {
   int l, s;
   std::vector<double> eps, O, v, W;  // O rows = eigenvectors; W = v O^T
@@ -84,9 +109,8 @@ struct wp_lattice {
   // finds it held (another thread on this lattice) allocates its own.
   std::mutex ws_mu;
   struct Solve64WS {
-    DBuf<double2> dG, dy, ds, dacap;
-    DBuf<int> dj0, dg0, dfin;
-    DBuf<double> dE;
+    DBuf<double2> dG, dy, ds;
+    DBuf<double> din;   // energies, then (int) on-shell bins, initial channels, finals
     DBuf<int64_t> g1w;
     wpcd::GraphCache chunk_graph[2];   // one full chunk of terms per capture slot
   } ws64;
@@ -177,14 +201,18 @@ struct MixedWork {
   int B = 0, m = 0, nfin = 0;
   int64_t R = 0, D = 0, DB = 0;
   bool fused = false, split = false;
-  DBuf<double2> dG64, db, dy, dr, dKy, ds64, dcap, dcoef, H, part, nrm;
+  DBuf<double2> dG64, db, dy, dr, dKy, ds64, dcoef, H, part, nrm;
   DBuf<float2> dG32, V, t32, kv32;
   DBuf<double> scl;
   DBuf<int> dj0, dfin, dg0;
   DBuf<double> dE;        // energies, G1 work list: used by solve_mixed only
   DBuf<int64_t> g1w;
-  std::vector<double2> hc, hH, hn, coef;
-  std::vector<double> hsc;
+  // host side of a cycle, in pinned memory: norms, Hessenberg columns and scales come in one launch, the
+  // coefficients leave from it and the captured U is written to it (from and to pageable memory each of the
+  // five copies of a cycle stopped the host and the stream for 20 to 40 us)
+  PinBuf pin;
+  double2 *hn = nullptr, *hH = nullptr, *coef = nullptr, *hc = nullptr;
+  double* hsc = nullptr;
   // launch choices of the current call (wp_solve_opts) and the graphs of the Arnoldi sweep
   // (index: the first cycle, whose residual is b, or a later one)
   int step_tile = 0, spmm_cols = 0;
