@@ -3133,17 +3133,17 @@ hipError_t launch_spmv_gen(int64_t rows, int nch, int B, const int64_t* rowptr, 
       pk.npk > nch * nch)
     return hipErrorInvalidValue;
   // The choice depends on B, the lattice and the options only, so every launch on a given batch width
-  // sums in one order. k_spmv_pk takes passes of up to 4 columns and is the better reader of a P0 that
-  // streams from HBM: 18 channels, M = N = 150, 4 columns, 180 us in FP32 (660 MB) against 212 us for
-  // the matrix-core kernel, whose loads touch a block in 32-byte pieces, and 309 us in FP64 (1.3 GB)
-  // against 348 us. Where P0 stays in the caches, or another pass over it would be needed, the
-  // matrix-core kernel is faster: M = N = 60, 4 columns, 40 us against 54 us in FP32 and 45 us against
-  // 83 us in FP64; 14 channels, M = N = 100, 3 columns, 49 us against 87 us and 101 us against 244 us;
-  // FP32 blocks on FP64 vectors at M = N = 150: 217 us against 251 us. An explicit spmm_cols below the
-  // call's column count asks for passes of 4. PackView.one_order: passes below 16 columns, then the
-  // 32-column window with a row's blocks summed in sequence (the same sums as one lane per column).
+  // sums in one order. PackView.one_order (all FP32 products): k_spmv_pk in passes of up to 4 columns below 16
+  // columns, then the 32-column window with a row's blocks summed in sequence (the same sums as one lane per
+  // column; 18 channels, M = N = 100, 32 columns FP32 283 us). Otherwise (FP64
+  // vectors) k_spmv_pk is the better reader of a P0 that streams from HBM: 18 channels, M = N = 150, 4 columns
+  // 309 us (1.3 GB) against 348 us for the matrix-core kernel, whose loads touch a block in 32-byte pieces. Where
+  // P0 stays in the caches, or another pass over it would be needed, the matrix-core kernel is faster: M = N =
+  // 60, 4 columns, 45 us against 83 us; 14 channels, M = N = 100, 3 columns 101 us against 244 us; FP32 blocks on
+  // FP64 vectors at M = N = 150: 217 us against 251 us. An explicit spmm_cols below the call's column count asks
+  // for passes of 4.
   constexpr bool same = sizeof(XT) == 2 * sizeof(VT);
-  const int64_t line = (sizeof(VT) == 4 ? (int64_t)256 : (int64_t)800) << 20;
+  const int64_t line = (int64_t)800 << 20;
   const bool passes = pk.one_order     ? B < (pk.spmm_min > 0 ? pk.spmm_min : 16) || nch > 24
                       : pk.spmm_min > 0 ? B < pk.spmm_min
                                         : same && (B <= 2 || B == 4) &&

@@ -16,12 +16,13 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // hi + lo split of a value: hi = bf16(x), lo = bf16(x - hi), each rounded to nearest even
 __device__ __forceinline__ void split_bf16(float x, __bf16& hi, __bf16& lo) {
+#pragma clang fp contract(off)   // x is a rounded product: a fused x - hi would be of the exact one
   hi = (__bf16)x;
   lo = (__bf16)(x - (float)hi);
 }
 
 // One channel g (pair wave w) and 8*CT complex columns (16*CT real columns: re/im of each):
-//   t = O y on MFMA 16x16x32 bf16, t *= G1 (FP32), s = (v O^T) t on MFMA, s written in FP32.
+//   t = O y on MFMA 16x16x16 bf16, t *= G1 (FP32), s = (v O^T) t on MFMA, s written in FP32.
 // SPLIT = false: y, t, O and v O^T rounded to bf16 once (one product per tile);
 // SPLIT = true: every operand x is carried as hi + lo with hi = bf16(x), lo = bf16(x - hi), and
 //   a tile product is A_hi B_hi + A_hi B_lo + A_lo B_hi (16 significant bits per operand).
@@ -40,6 +41,15 @@ __device__ __forceinline__ void split_bf16(float x, __bf16& hi, __bf16& lo) {
 // 16x16x16 products: 47 -> 28.5 us at the sizes above, 27 -> 20 us
 // at 2 channels, M = N = 100, 64 columns and 17 -> 8 us at one, 121 -> 21 us at 1 channel, M = 400,
 // N = 300, 4 columns (with events around each launch).
+// one half (q) of a 32-wide k step
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, int q, f32x4 c) {
+  const s16x8 x = __builtin_bit_cast(s16x8, a), z = __builtin_bit_cast(s16x8, b);
+  return q == 0 ? __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_shufflevector(x, x, 0, 1, 2, 3),
+                                                            __builtin_shufflevector(z, z, 0, 1, 2, 3), c, 0, 0, 0)
+                : __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_shufflevector(x, x, 4, 5, 6, 7),
+                                                            __builtin_shufflevector(z, z, 4, 5, 6, 7), c, 0, 0, 0);
+}
+
 template <bool SPLIT, int CT, int TPW, int D>
 __global__ void __launch_bounds__(1024) k_step_bf16(RotArgsMixed r, const float2* __restrict__ y,
                                                     float2* __restrict__ s_out, int nt, int ns) {
@@ -90,16 +100,14 @@ __global__ void __launch_bounds__(1024) k_step_bf16(RotArgsMixed r, const float2
       if (SPLIT) bl = *reinterpret_cast<const bf16x8*>(bp + RC * KS);
 #pragma unroll
       for (int h = 0; h < TPW; ++h) {
-        if constexpr (SPLIT) {
-          acc[h][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[h][0], bh, acc[h][ct], 0, 0, 0);
-          acc[h][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[h][0], bl, acc[h][ct], 0, 0, 0);
-          acc[h][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[h][1], bh, acc[h][ct], 0, 0, 0);
-        } else {
-          const s16x8 x = __builtin_bit_cast(s16x8, a[h][0]), z = __builtin_bit_cast(s16x8, bh);
-          acc[h][ct] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_shufflevector(x, x, 0, 1, 2, 3),
-                                                                 __builtin_shufflevector(z, z, 0, 1, 2, 3), acc[h][ct], 0, 0, 0);
-          acc[h][ct] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_shufflevector(x, x, 4, 5, 6, 7),
-                                                                 __builtin_shufflevector(z, z, 4, 5, 6, 7), acc[h][ct], 0, 0, 0);
+        // k in ascending order, high x high, high x low and low x high parts per 16 of it
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          acc[h][ct] = mfma16(a[h][0], bh, q, acc[h][ct]);
+          if (SPLIT) {
+            acc[h][ct] = mfma16(a[h][0], bl, q, acc[h][ct]);
+            acc[h][ct] = mfma16(a[h][NP - 1], bh, q, acc[h][ct]);
+          }
         }
       }
     }
@@ -797,7 +805,7 @@ hipError_t launch_arnoldi_product(const ArnoldiArgs& a, const float2* t, float2*
   if (a.B >= 16 && a.nch <= 4) {
     ProfScope ps("spmm_arnoldi", s);
     int nb;
-    if (a.pk.one_order) {
+    if (!a.split) {
       const dim3 grid = arn_grid(a.cells, a.B, a.nblk, 1);
       switch (a.nch) {
         case 1: spmm_arn_launch<1>(grid, s, a.cells, a.B, a.rowptr, a.col, a.val, a.order, t, a.V, a.vstride, a.j, a.scl, a.part); break;
@@ -842,7 +850,7 @@ hipError_t launch_arnoldi_product(const ArnoldiArgs& a, const float2* t, float2*
       if (e != hipSuccess) return e;
     }
     ProfScope ps("arnoldi_dots", s);
-    const dim3 grid = arn_grid(rows, a.B, a.nblk, a.pk.one_order ? 1 : arn_rows(a.B));
+    const dim3 grid = arn_grid(rows, a.B, a.nblk, a.split ? arn_rows(a.B) : 1);
     if (a.m <= 8)
       hipLaunchKernelGGL(k_sub_dots<8>, grid, dim3(256), 0, s, rows, a.B, kv_scratch, a.V, a.vstride, a.j, a.scl, a.part);
     else
@@ -856,7 +864,7 @@ hipError_t launch_arnoldi_product(const ArnoldiArgs& a, const float2* t, float2*
 hipError_t launch_arnoldi_orth(const ArnoldiArgs& a, hipStream_t s) {
   if (a.j < 0 || a.j + 1 > ARN_NV || a.j + 1 > a.m) return hipErrorInvalidValue;
   const int64_t rows = a.cells * a.nch;
-  const dim3 grid = arn_grid(rows, a.B, a.nblk, a.pk.one_order ? 1 : arn_rows(a.B));
+  const dim3 grid = arn_grid(rows, a.B, a.nblk, a.split ? arn_rows(a.B) : 1);
   const double2* hcol = a.H + (size_t)a.j * (a.m + 1) * a.B;
   if (a.m <= 8)
     hipLaunchKernelGGL(k_orth_norm<8>, grid, dim3(256), 0, s, rows, a.B, a.V, a.vstride, a.j, hcol, a.scl, a.part);

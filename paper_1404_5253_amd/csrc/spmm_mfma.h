@@ -10,8 +10,8 @@
 // 16-row tile, and their operands are what the loads deliver: lane = (4-row tile, row) for P0,
 // lane = real column for x.
 //
-// Measured at 18 channels, M = N = 100 (250 k blocks), 32 columns: FP32 230 us (1.4 GB of P0 and
-// gathered x, 6.2 TB/s) and FP32 blocks on FP64 vectors 384 us; lanes over the columns with every block
+// Measured at 18 channels, M = N = 100 (250 k blocks), 32 columns: FP32 283 us (1.4 GB of P0 and
+// gathered x, 5 TB/s) and FP32 blocks on FP64 vectors 384 us; lanes over the columns with every block
 // staged in LDS took 2276 and 2428 us (half the lanes idle at 32 columns, one block in flight). At 14
 // channels, 6 columns, FP64: 120 us, against 275 us for two passes of 4 columns.
 #pragma once
@@ -57,66 +57,41 @@ __device__ __forceinline__ int64_t uniform(int64_t v) {
 }
 
 // FP32 blocks and vectors on v_mfma_f32_4x4x1 (16 products of 4 rows x 4 columns, one k): with A
-// broadcast over the S = CW / 2 products that share a P0 block (cbsz = log2 S), one instruction adds
-// P0[4 rows][u] x[u][2 CW real columns] for G = 32 / CW blocks at once. A wavefront takes a window
-// of CW complex columns of one block row, G blocks per pass; lane = group (block of the pass) x real
-// column. Register n of the pass holds, in slot s of a group, the 4 RPL-row units q of block column u
-// with u NQ + q = n S + s. The x values of the next pass are loaded before the row sums of the
-// current one are finished. WR wavefronts share a block row (4 for the wide windows, whose one or two
-// blocks per pass would leave the longest rows, several times the median, at the end of the launch);
-// their sums are added in LDS.
-template <int NC, int CW>
+// broadcast over the 16 products (cbsz = 4), one instruction adds P0[4 rows][u] x[u][64 real columns]. A
+// wavefront takes a window of 32 complex columns of a block row, its blocks in order (PackView.one_order);
+// lane = real column. Register n of a block holds, in slot s of a quad of lanes, the 4 RPL-row units q of block
+// column u with u NQ + q = 16 n + s. The x values of the next block are loaded before the row sums of the
+// current one are finished. (Four wavefronts sharing a block row took 232 us where this takes 283 at 18
+// channels, M = N = 100, 32 columns, but sum in another order.)
+template <int NC>
 constexpr int regs_f32() {
-  constexpr int r = rows_per_load(NC), q = row_units(NC), n = (NC * q + CW / 2 - 1) / (CW / 2);
+  constexpr int r = rows_per_load(NC), q = row_units(NC), n = (NC * q + 15) / 16;
   return n * r + n + NC + 8 * q * r;
 }
-template <int NC, int CW, int WR>
-__global__ void __launch_bounds__(256, waves_for(regs_f32<NC, CW>())) k_spmm_f32(int64_t rows, int B, int cb0, int cb1,
+template <int NC>
+__global__ void __launch_bounds__(256, waves_for(regs_f32<NC>())) k_spmm_f32(int64_t rows, int B, int cb0, int cb1,
                                                      const int64_t* __restrict__ rowptr,
                                                      const int32_t* __restrict__ col, const float* __restrict__ val,
                                                      int npk, const int* __restrict__ pkt, const float* __restrict__ x,
                                                      float* __restrict__ y, const int32_t* __restrict__ order) {
-  constexpr int RPL = rows_per_load(NC), NQ = row_units(NC), T = NC * NQ;
-  constexpr int S = CW / 2, GL = 2 * CW, G = 64 / GL, NL = (T + S - 1) / S;
-  constexpr int CBSZ = S == 16 ? 4 : S == 8 ? 3 : S == 4 ? 2 : 1;
-  constexpr int V = (4 * NQ * RPL + G - 1) / G * G;   // row sums, dealt out to the groups
+  constexpr int RPL = rows_per_load(NC), NQ = row_units(NC), T = NC * NQ, S = 16, NL = (T + S - 1) / S;
   using VR = typename RowsOf<RPL>::T;
-  const int lane = threadIdx.x & 63;
-  const int grp = lane / GL, rl = lane % GL, i4 = lane & 3;
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wr = WR == 4 ? wv : 0;
-  const int64_t W = (int64_t)gridDim.x * (4 / WR), w = WR == 4 ? blockIdx.x : (int64_t)blockIdx.x * 4 + wv;
-  const int c0 = cb0 + blockIdx.y * CW;
-  const int cr = 2 * c0 + rl;                    // real column of the lane
+  const int lane = threadIdx.x & 63, i4 = lane & 3;
+  const int64_t W = (int64_t)gridDim.x * 4, w = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c0 = cb0 + blockIdx.y * 32;
+  const int cr = 2 * c0 + lane;                  // real column of the lane
   const bool live = cr < 2 * cb1;
   const int crc = live ? cr : 2 * cb1 - 1;       // columns past the end are computed and not stored
-  // packed position of the lane's rows in every register of a pass; rows that are not stored read
+  // packed position of the lane's rows in every register of a block; rows that are not stored read
   // position 0 and count as zero
   int moff[NL];
   bool mok[NL];
 #pragma unroll
   for (int n = 0; n < NL; ++n) {
-    const int t = n * S + (rl >> 2);
+    const int t = n * S + (lane >> 2);
     const int u = t < T ? t / NQ : 0, r = RPL * (4 * (t - u * NQ) + i4);
     mok[n] = t < T && r >= pkt[NC + u] && r < pkt[2 * NC + u];
     moff[n] = mok[n] ? pkt[3 * NC + u] - pkt[NC + u] + r : 0;
-  }
-  // after the sums are dealt out, value k of the lane is row orow[k] of the block row
-  constexpr int VO = V / G;
-  __shared__ float red[WR == 4 ? 4 : 1][WR == 4 ? VO : 1][64];
-  int och[VO];
-  {
-    int base = 0, n = V;
-#pragma unroll
-    for (int d = 32; d >= GL; d >>= 1) {
-      n /= 2;
-      if (lane & d) base += n;
-    }
-#pragma unroll
-    for (int k = 0; k < VO; ++k) {
-      const int id = base + k, a = id >> 2, q = a / RPL, j = a - q * RPL;
-      const int r = RPL * (4 * q + (id & 3)) + j;
-      och[k] = r < NC ? pkt[r] : -1;
-    }
   }
   const int64_t xst = 2 * (int64_t)B;
   float xv[NC];
@@ -129,7 +104,7 @@ __global__ void __launch_bounds__(256, waves_for(regs_f32<NC, CW>())) k_spmm_f32
   int64_t row = uniform(stripe_row(rows, W, w, s, order));
   if (row < 0) return;
   int64_t b0 = rowptr[row], b1 = rowptr[row + 1];
-  if (b0 + wr * G < b1) load_x(col[min(b0 + wr * G + grp, b1 - 1)]);
+  if (b0 < b1) load_x(col[b0]);
   while (true) {
     const int64_t nrow = uniform(stripe_row(rows, W, w, ++s, order));
     const int64_t n0 = nrow >= 0 ? rowptr[nrow] : 0, n1 = nrow >= 0 ? rowptr[nrow + 1] : 0;
@@ -137,30 +112,29 @@ __global__ void __launch_bounds__(256, waves_for(regs_f32<NC, CW>())) k_spmm_f32
 #pragma unroll
     for (int a = 0; a < NQ * RPL; ++a) acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float* vp = val + b0 * npk;
-    if (b0 + wr * G >= b1 && n0 + wr * G < n1) load_x(col[min(n0 + wr * G + grp, n1 - 1)]);
-    for (int64_t cb = b0 + wr * G; cb < b1; cb += WR * G) {
-      const bool ok = cb + grp < b1;
-      const unsigned eo = ok ? (unsigned)(cb - b0 + grp) * (unsigned)npk : 0u;
-      // the block column of the lane's block in the next pass (of this row or of the next one)
-      const bool more = cb + WR * G < b1;
-      const int64_t f0 = more ? cb + WR * G : n0 + wr * G, f1 = more ? b1 : n1;
+    if (b0 >= b1 && n0 < n1) load_x(col[n0]);
+    for (int64_t cb = b0; cb < b1; ++cb) {
+      const unsigned eo = (unsigned)(cb - b0) * (unsigned)npk;
+      // the next block (of this row or of the next one)
+      const bool more = cb + 1 < b1;
+      const int64_t f0 = more ? cb + 1 : n0, f1 = more ? b1 : n1;
       VR a[NL];
 #pragma unroll
       for (int n = 0; n < NL; ++n) a[n] = *reinterpret_cast<const VR*>(vp + (eo + (unsigned)moff[n]));
-      const int32_t cn = f0 < f1 ? col[min(f0 + grp, f1 - 1)] : 0;
+      const int32_t cn = f0 < f1 ? col[f0] : 0;
 #pragma unroll
       for (int n = 0; n < NL; ++n) {
         float av[RPL];
 #pragma unroll
-        for (int j = 0; j < RPL; ++j) av[j] = (ok && mok[n]) ? part(a[n], j) : 0.f;
+        for (int j = 0; j < RPL; ++j) av[j] = mok[n] ? part(a[n], j) : 0.f;
         // the slots of the register: the broadcast index has to be a literal
 #define WP_SLOT(sl)                                                                                          \
-  if constexpr (sl < S) {                                                                                    \
+  {                                                                                                          \
     const int t = n * S + sl;                                                                                \
     if (t < T) {                                                                                             \
       const int u = t / NQ, q = t - u * NQ;                                                                  \
       _Pragma("unroll") for (int j = 0; j < RPL; ++j)                                                        \
-        acc[q * RPL + j] = __builtin_amdgcn_mfma_f32_4x4x1f32(av[j], xv[u], acc[q * RPL + j], CBSZ, sl, 0);  \
+        acc[q * RPL + j] = __builtin_amdgcn_mfma_f32_4x4x1f32(av[j], xv[u], acc[q * RPL + j], 4, sl, 0);     \
     }                                                                                                        \
   }
         WP_SLOT(0) WP_SLOT(1) WP_SLOT(2) WP_SLOT(3) WP_SLOT(4) WP_SLOT(5) WP_SLOT(6) WP_SLOT(7)
@@ -169,38 +143,12 @@ __global__ void __launch_bounds__(256, waves_for(regs_f32<NC, CW>())) k_spmm_f32
       }
       if (f0 < f1) load_x(cn);
     }
-    // sums over the groups, dealt out: each step halves the values a lane holds
-    float v[V];
+    // value k of the lane: row RPL (4 q + k mod 4) + j of the block row, in accumulator q RPL + j
 #pragma unroll
-    for (int k = 0; k < V; ++k) v[k] = k < 4 * NQ * RPL ? acc[k >> 2][k & 3] : 0.f;
-    {
-      int n = V;
-#pragma unroll
-      for (int d = 32; d >= GL; d >>= 1) {
-        n /= 2;
-        const bool hi = (lane & d) != 0;
-#pragma unroll
-        for (int k = 0; k < V / 2; ++k)
-          if (k < n) {
-            const float keep = hi ? v[k + n] : v[k], send = hi ? v[k] : v[k + n];
-            v[k] = keep + __shfl_xor(send, d, 64);
-          }
-      }
+    for (int k = 0; k < 4 * NQ * RPL; ++k) {
+      const int ac = k >> 2, q = ac / RPL, r = RPL * (4 * q + (k & 3)) + ac - q * RPL;
+      if (r < NC && live) y[((int64_t)row * NC + pkt[r]) * xst + cr] = acc[ac][k & 3];
     }
-    if constexpr (WR == 4) {
-#pragma unroll
-      for (int k = 0; k < VO; ++k) red[wv][k][lane] = v[k];
-      __syncthreads();
-    }
-#pragma unroll
-    for (int k = 0; k < VO; ++k) {
-      if (WR == 4) {   // value k is finished by wavefront k mod 4
-        if ((k & 3) != wv) continue;
-        v[k] = (red[0][k][lane] + red[1][k][lane]) + (red[2][k][lane] + red[3][k][lane]);
-      }
-      if (live && och[k] >= 0) y[((int64_t)row * NC + och[k]) * xst + cr] = v[k];
-    }
-    if constexpr (WR == 4) __syncthreads();
     if (nrow < 0) break;
     row = nrow;
     b0 = n0;
@@ -212,7 +160,8 @@ __global__ void __launch_bounds__(256, waves_for(regs_f32<NC, CW>())) k_spmm_f32
 // lane = k 16 + product 4 + (row of A | column of B); D has lane = row 16 + product 4 + column. GB = 4:
 // the four products are four P0 blocks of the row, each with 4 H complex columns; GB = 1: one block
 // with 16 H complex columns. h = 0 .. H - 1 takes complex columns (4 or 16) h + lane column, real and
-// imaginary part as two B operands. WR as above.
+// imaginary part as two B operands. WR wavefronts share a block row (4 where its one or two blocks per pass would
+// leave the longest rows, several times the median, at the end of the launch); their sums are added in LDS.
 template <int CTRL>
 __device__ __forceinline__ double row_rotated(double v) {   // within rows of 16 lanes
   const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
@@ -357,29 +306,15 @@ inline int spmm_window(int B, int spmm_min) {
 }
 // The narrow windows share a block row among four wavefronts until the rows alone fill the device:
 // 10 channels, M = N = 40, 4 columns, FP64: 12 us shared, 22 us not; 18 channels, M = N = 150, 8
-// columns: 441 us shared, 406 us not (FP32 232 and 224; at M = N = 100 103 and 114).
+// columns: 441 us shared, 406 us not.
 inline bool shared_rows(int64_t rows) { return rows < 16384; }
 
 template <int NC>
 void launch_nc(int64_t rows, int B, int cb0, int cb1, const int64_t* rowptr, const int32_t* col, const float* val, int npk,
-               const int* pkt, const float2* x, float2* y, const int32_t* order, int window, bool one_order, hipStream_t s) {
-  const float* xr = reinterpret_cast<const float*>(x);
-  float* yr = reinterpret_cast<float*>(y);
-#define WP_W(cw, wr)                                                                                           \
-  {                                                                                                            \
-    static const int per_cu = resident(k_spmm_f32<NC, cw, wr>);                                                \
-    hipLaunchKernelGGL((k_spmm_f32<NC, cw, wr>), spmm_grid(rows, per_cu, wr, cb1 - cb0, cw), dim3(256), 0, s,  \
-                       rows, B, cb0, cb1, rowptr, col, val, npk, pkt, xr, yr, order);                          \
-  }
-  const bool sh = shared_rows(rows);
-  if (window <= 4 && sh) WP_W(4, 4)
-  else if (window <= 4) WP_W(4, 1)
-  else if (window <= 8 && sh) WP_W(8, 4)
-  else if (window <= 8) WP_W(8, 1)
-  else if (one_order) WP_W(32, 1)
-  else if (window <= 16) WP_W(16, 4)
-  else WP_W(32, 4)
-#undef WP_W
+               const int* pkt, const float2* x, float2* y, const int32_t* order, int, bool, hipStream_t s) {
+  static const int per_cu = resident(k_spmm_f32<NC>);
+  hipLaunchKernelGGL(k_spmm_f32<NC>, spmm_grid(rows, per_cu, 1, cb1 - cb0, 32), dim3(256), 0, s, rows, B, cb0, cb1,
+                     rowptr, col, val, npk, pkt, reinterpret_cast<const float*>(x), reinterpret_cast<float*>(y), order);
 }
 
 template <int NC, typename VT>

@@ -253,10 +253,11 @@ struct PackView {
   const int* pkt = nullptr;
   int spmm_min = 0;
   int64_t blocks = 0;   // stored blocks of the resident P0
-  // products of the unsplit mixed mode: one order of summation per column count. Its BF16 operands
-  // are rounded once, so another order of the sums moves some of them to the other neighbour and
-  // the refinement takes another path: with several orders in use, solves that stop at an estimate of
-  // 1e-10 differed by up to 1.5e-9, with one they do not.
+  // one order of summation per column count: the FP32 products of the refinement, whose operands are then
+  // rounded to BF16 (or BF16 pairs). Another order of the sums rounds some of them to the other neighbour, and
+  // a column then stops elsewhere, now and then a cycle earlier: solves that stop at an estimate of 1e-10
+  // differed by up to 1.5e-9 (unsplit) and 7e-9 (split, 8 in 300), with one order by 1e-10 at most. Also the
+  // residuals of the unsplit mode.
   bool one_order = false;
 };
 // Many channels (spmm_mfma.h).
@@ -355,6 +356,7 @@ struct ArnoldiArgs {
   double2* part;        // [nblk][ARN_NV][B] partial sums
   int nblk;
   PackView pk;          // packed blocks (many channels)
+  bool split;           // BF16 pairs: the partial sums may follow the grid (unsplit: one order)
 };
 // w = V_j - P0 t into slot j + 1 and H column j (rows 0..j); kv_scratch ([rows][B]) is used when
 // the fused kernel does not apply (B < 16 or nch > 4)
