@@ -1667,7 +1667,10 @@ __device__ __forceinline__ double2 step_g1(const RotArgs& r, int g, int k, int j
   return r.G[(((size_t)jj * r.M + (k < r.M ? k : 0)) * r.nch + g) * r.B + cb];
 }
 // One accumulator value: (k, real column) of t, its complex partner in lane ^ 1. Captures e0^T O y and
-// returns the real or imaginary part of G1 t.
+// returns the real or imaginary part of G1 t. Which product of the imaginary part is rounded on its own is spelled
+// out (IM: im G1_re is fused last, else re G1_im): the Pade sums of a divergent series amplify a last bit of it to
+// 1e-9 of the amplitude, so a compiler's choice between the two would show.
+template <bool IM>
 __device__ __forceinline__ double step_scale(const RotArgs& r, int g, int k, bool live, int jj, int cb, int part,
                                              double val, double2 gv) {
   const double other = __shfl_xor(val, 1, WARP);
@@ -1677,7 +1680,8 @@ __device__ __forceinline__ double step_scale(const RotArgs& r, int g, int k, boo
     for (int f = 0; f < r.nfin; ++f)
       if (r.finals[f] == g) r.acap[r.acap_off + (int64_t)cb * r.nfin + f] = make_double2(re, im);
   }
-  return part ? (re * gv.y + im * gv.x) : (re * gv.x - im * gv.y);
+  const double pr = im * gv.y, pi = IM ? re * gv.y : im * gv.x;
+  return part ? (IM ? fma(im, gv.x, pi) : fma(re, gv.y, pi)) : fma(re, gv.x, -pr);
 }
 
 template <int CT, int TPW, int D>
@@ -1740,7 +1744,7 @@ __global__ void __launch_bounds__(1024) k_step64m(RotArgs r, const double2* __re
         for (int v = 0; v < 4; ++v) gv[v] = step_g1(r, g, k0 + 4 * v, jj[ct], cb[ct]);
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        acc[h][ct][v] = step_scale(r, g, k0 + 4 * v, live[ct], jj[ct], cb[ct], part, acc[h][ct][v], gv[v]);
+        acc[h][ct][v] = step_scale<true>(r, g, k0 + 4 * v, live[ct], jj[ct], cb[ct], part, acc[h][ct][v], gv[v]);
       if (!AHEAD) __builtin_amdgcn_sched_barrier(0);   // one tile's G1 in flight (registers)
     }
   __syncthreads();   // every wavefront has read Y
@@ -1819,7 +1823,7 @@ __global__ void __launch_bounds__(1024) k_step64q(RotArgs r, const double2* __re
   for (int h = 0; h < TPW; ++h)
 #pragma unroll
     for (int q = 0; q < Q; ++q)
-      acc[h][q] = step_scale(r, g, (wv + h * nw) * 16 + drow, live[q], jj[q], cb[q], part, acc[h][q], gv[h][q]);
+      acc[h][q] = step_scale<false>(r, g, (wv + h * nw) * 16 + drow, live[q], jj[q], cb[q], part, acc[h][q], gv[h][q]);
   __syncthreads();   // every wavefront has read Y
 #pragma unroll
   for (int h = 0; h < TPW; ++h)
