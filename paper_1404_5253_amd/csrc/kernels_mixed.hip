@@ -29,18 +29,18 @@ __device__ __forceinline__ void split_bf16(float x, __bf16& hi, __bf16& lo) {
 // Accumulation is FP32 throughout.
 // MFMA operands: lane l holds row l%16 of A and column l%16 of B at the 8 k of its quarter q = l/16; within
 // a block of 32 these are 4q .. 4q+3 and 16+4q .. 16+4q+3, the order in which the fragment tables and the
-// LDS tile hold them, so that one 16-byte read serves one 16x16x32 product (SPLIT) or two 16x16x16
-// products in ascending k. The result is D[4(l/16)+r][l%16], r = 0..3.
+// LDS tile hold them, so that one 16-byte read serves two 16x16x16 products in ascending k (one 16x16x32
+// instruction would be 1 to 3 us faster at the sizes below, but sums in another order: a refinement's columns
+// then stop elsewhere). The result is D[4(l/16)+r][l%16], r = 0..3.
 // The products are a small part of the time (18 channels, M = N = 150, 4 columns: 6.6 GFLOP); what counts
 // is how many loads are under way. O and v O^T come as fragment tables (launch_pack_bf16): for row tile
 // kt and k step s of 32, the hi then the lo operands of the 64 lanes, 16 bytes each, read D steps ahead
 // and first before y is staged. The wavefronts share the row tiles, TPW each, with all accumulators in
 // registers, so one LDS tile [real column][k] serves as Y and then as T; a thread stages four
 // neighbouring k of one column. Rows of the LDS tile are Kp + 8 entries long: 16 lanes reading 16
-// bytes of 16 columns then fall on all banks. Measured against two LDS tiles, row-major tables and
-// 16x16x16 products: 47 -> 28.5 us at the sizes above, 27 -> 20 us
-// at 2 channels, M = N = 100, 64 columns and 17 -> 8 us at one, 121 -> 21 us at 1 channel, M = 400,
-// N = 300, 4 columns (with events around each launch).
+// bytes of 16 columns then fall on all banks. Measured (split; with events around each launch) against two
+// LDS tiles and row-major tables: 47 -> 30 us at the sizes above, 27 -> 21 us at 2 channels, M = N = 100, 64
+// columns and 17 -> 8 us at one, 121 -> 22 us at 1 channel, M = 400, N = 300, 4 columns.
 // one half (q) of a 32-wide k step
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, int q, f32x4 c) {
   const s16x8 x = __builtin_bit_cast(s16x8, a), z = __builtin_bit_cast(s16x8, b);
