@@ -1055,12 +1055,12 @@ static wp_status solve_fp64(wp_lattice* L, const std::vector<double>& Elab, cons
       if (L->pin) (void)hipHostFree(L->pin);
       L->pin = nullptr;
       L->pin_cap = 0;
-      HIPCHECK(hipHostMalloc((void**)&L->pin, pin_n * sizeof(double2), hipHostMallocDefault));
+      HIPCHECK(hipHostMalloc((void**)&L->pin, pin_n * sizeof(double2), hipHostMallocCoherent));
       L->pin_cap = pin_n;
     }
     pin = L->pin;
   } else {   // another call on this lattice holds the shared buffer
-    HIPCHECK(hipHostMalloc((void**)&own, pin_n * sizeof(double2), hipHostMallocDefault));
+    HIPCHECK(hipHostMalloc((void**)&own, pin_n * sizeof(double2), hipHostMallocCoherent));
     pin = own;
   }
   struct PinGuard {   // the stream drains before the staging buffer is released (also on errors)

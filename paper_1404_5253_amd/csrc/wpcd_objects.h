@@ -36,14 +36,15 @@ using namespace wpcd;
     if (e_ != hipSuccess) return wpcd::fail(WP_EDEVICE, std::string(#expr) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
-// Pinned host memory, grow-only; device kernels write it and copies to the device read it.
+// Pinned host memory, grow-only; device kernels write it (coherent: seen once their stream or event is waited
+// for) and copies to the device read it.
 struct PinBuf {
   double2* p = nullptr;
   size_t n = 0;
   bool grow(size_t k) {
     if (n >= k) return true;
     reset();
-    if (hipHostMalloc((void**)&p, k * sizeof(double2), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc((void**)&p, k * sizeof(double2), hipHostMallocCoherent) != hipSuccess) {
       p = nullptr;
       return false;
     }
