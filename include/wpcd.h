@@ -237,8 +237,9 @@ wp_status perm_matrix_export(const wp_lattice* lat, int64_t* row_ptr, int32_t* c
  *   step_tile: FP64 step kernel, one of WP_STEP_*; a choice whose tiles do not fit the lattice
  *              (LDS, rows) falls back to the default.
  *   spmm_cols: more than 4 channels: the column count of a call from which the block-CSR
- *              products take windows of 32 columns, and below which passes of 4 (default 0: FP64
- *              vectors: the window follows the column count; FP32: 16).
+ *              products add a row's blocks one after another (up to 24 channels), and below which
+ *              they take passes of 4 columns (default 0: 16, and FP64 vectors below it on the
+ *              matrix cores with the sums of the passes).
  */
 enum { WP_SOLVE_FP64 = 0, WP_SOLVE_MIXED = 1, WP_SOLVE_MIXED_SPLIT = 2 };
 enum { WP_STEP_AUTO = 0, WP_STEP_MFMA8 = 1, WP_STEP_MFMA16 = 2, WP_STEP_VALU = 3, WP_STEP_ROWS = 4 };

@@ -174,7 +174,7 @@ static wp_status admit_run(wp_batch* b, int n, const double* E_lab, hipStream_t 
     HIPCHECK(launch_init_rhs64(L->M, L->N, L->nch, B, L->d_W.p, L->d_wave.p, w.dj0.p, b->dg0.p, w.ds64.p, st, c0, c1));
     WP_LAUNCH("spmv_f32v_f64x", st,
               launch_spmv_f32v_f64x(R, L->nch, B, L->d_rowptr.p, L->d_col.p, L->d_val32.p, w.ds64.p, w.db.p, st, c0,
-                                    c1, spmv_order(L), pk_view(L, b->o.spmm_cols, !w.split)));
+                                    c1, spmv_order(L), pk_view(L, b->o.spmm_cols)));
     HIPCHECK(launch_fill0_cols(w.dy.p, b->D, B, c0, c1, st));
     for (int e = 0; e < k; ++e) b->s[sl0 + e].mc.assign(nf, MixedCol());
   } else {

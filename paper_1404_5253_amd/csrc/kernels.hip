@@ -2929,7 +2929,7 @@ __device__ __forceinline__ float vget(const float2& v, int k) { return k ? v.y :
 __device__ __forceinline__ double vget(const double& v, int) { return v; }
 __device__ __forceinline__ float vget(const float& v, int) { return v; }
 
-// Few columns (B <= 4, or passes of 4 on request; more columns: spmm_mfma.h): one wavefront per
+// Passes of up to 4 columns (which calls take them: launch_spmv_gen): one wavefront per
 // block row (rows in the order given, longest first).
 // Lanes over (slot s, h): a slot takes one block of the pass (SL blocks per pass), lane h of the
 // slot owns the RPL channel rows RPL h .. RPL h + RPL - 1 (positions) and reads, for every block
@@ -2945,11 +2945,11 @@ __global__ void __launch_bounds__(256) k_spmv_pk(int64_t rows, int B, int cb0, i
                                                  const VT* __restrict__ val, int npk, const int* __restrict__ pkt,
                                                  const XT* __restrict__ x, XT* __restrict__ y,
                                                  const int32_t* __restrict__ order) {
-  constexpr int RPL = (NC % 2 == 0) ? 2 : 1;
+  constexpr int RPL = pk_rows(NC);
   // staging unit: one complex entry, or (P2) two adjacent columns as one 16-byte entry
   using ST = typename std::conditional<P2, float4, XT>::type;
   constexpr int SPC = P2 ? CT / 2 : CT;   // staging units per (slot, column u)
-  constexpr int NH = NC / RPL, SL = 64 / NH, PER = NC * SPC, NST = (SL * PER + 63) / 64;
+  constexpr int NH = NC / RPL, SL = pk_slots(NC), PER = NC * SPC, NST = (SL * PER + 63) / 64;
   static_assert(NC % UN == 0, "UN must divide NC");
   static_assert(!P2 || (CT % 2 == 0 && sizeof(XT) == 8), "pairs of complex FP32 columns only");
   using VR = typename VecR<VT, RPL>::T;
@@ -3136,23 +3136,22 @@ hipError_t launch_spmv_gen(int64_t rows, int nch, int B, const int64_t* rowptr, 
   if (cb0 < 0 || cb1 > B || cb0 >= cb1 || rows < 1 || nch < 5 || nch > PK_MAX || !pk.pkt || pk.npk < 1 ||
       pk.npk > nch * nch)
     return hipErrorInvalidValue;
-  // The choice depends on B, the lattice and the options only, so every launch on a given batch width
-  // sums in one order. PackView.one_order (all FP32 products): k_spmv_pk in passes of up to 4 columns below 16
-  // columns, then the 32-column window with a row's blocks summed in sequence (the same sums as one lane per
-  // column; 18 channels, M = N = 100, 32 columns FP32 283 us). Otherwise (FP64
-  // vectors) k_spmv_pk is the better reader of a P0 that streams from HBM: 18 channels, M = N = 150, 4 columns
-  // 309 us (1.3 GB) against 348 us for the matrix-core kernel, whose loads touch a block in 32-byte pieces. Where
-  // P0 stays in the caches, or another pass over it would be needed, the matrix-core kernel is faster: M = N =
-  // 60, 4 columns, 45 us against 83 us; 14 channels, M = N = 100, 3 columns 101 us against 244 us; FP32 blocks on
-  // FP64 vectors at M = N = 150: 217 us against 251 us. An explicit spmm_cols below the call's column count asks
-  // for passes of 4.
-  constexpr bool same = sizeof(XT) == 2 * sizeof(VT);
+  // The order of the sums depends on B and the options only, and is the same in every kernel that may run, so the
+  // choice between them changes no bit of a result: block after block from 16 columns on (spmm_cols: from that count
+  // on), by slots (pk_slots) below, and with more than 24 channels always.
+  const bool blockwise = B >= (pk.spmm_min > 0 ? pk.spmm_min : 16) && nch <= 24;
+  // By slots, FP32 vectors take k_spmv_pk in passes of up to 4 columns, and FP64 vectors on request (spmm_cols above
+  // the column count) and where it is the better reader of a P0 that streams from HBM: one or two columns, or 4 of
+  // more than 12 channels, where it loads 5 or 6 block columns at a time. Us, k_spmv_pk / matrix cores, FP64 blocks:
+  // 18 channels, 4 columns: 177 / 153 at 525 MB (M = N = 100), 197 / 186 at 647, 225 / 236 at 839, 310 / 347 at
+  // 1263; 2 columns 168 / 148 and 277 / 329 at 525 and 1263 MB. 10 channels, 2 columns: 88 / 84 at 283, 167 / 169 at
+  // 568, 288 / 301 at 1039; 4 columns 445 / 315 there. Two block columns at a time: 14 channels, 3 columns 265 / 113
+  // at 354 MB; 26 channels, 2 columns 653 / 467 at 1949. FP32 blocks: 251 / 213 at 18 channels, M = N = 150.
   const int64_t line = (int64_t)800 << 20;
-  const bool passes = pk.one_order     ? B < (pk.spmm_min > 0 ? pk.spmm_min : 16) || nch > 24
-                      : pk.spmm_min > 0 ? B < pk.spmm_min
-                                        : same && (B <= 2 || B == 4) &&
-                                              pk.blocks * pk.npk * (int64_t)sizeof(VT) > line;
-  if (!passes) return launch_spmm_pk(rows, nch, B, rowptr, col, val, x, y, s, cb0, cb1, order, pk);
+  const bool reader = std::is_same<VT, double>::value && (nch % 5 == 0 || nch % 6 == 0) && nch <= 24 &&
+                      (B <= 2 || (B == 4 && nch > 12)) && pk.blocks * pk.npk * (int64_t)sizeof(VT) > line;
+  if (blockwise || (std::is_same<XT, double2>::value && pk.spmm_min <= B && !reader))
+    return launch_spmm_pk(rows, nch, B, rowptr, col, val, x, y, s, cb0, cb1, order, pk, blockwise);
   const dim3 grid((unsigned)spmv_blocks(rows, order));
   switch (nch) {
 #define WP_PK_CASE(n) \

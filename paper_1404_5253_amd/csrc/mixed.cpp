@@ -134,7 +134,7 @@ wp_status wpcd::mixed_cycle(MixedWork& w, hipStream_t s, bool y_is_zero, const s
       {
         ProfScope ps("spmv_f32v_f64x", st);
         e = launch_spmv_f32v_f64x(R, nch, B, L->d_rowptr.p, L->d_col.p, L->d_val32.p, w.ds64.p, w.dKy.p, st, 0, -1,
-                                  spmv_order(L), pk_view(L, w.spmm_cols, !w.split));
+                                  spmv_order(L), pk_view(L, w.spmm_cols));
       }
       if (e != hipSuccess) return e;
       {
@@ -146,7 +146,7 @@ wp_status wpcd::mixed_cycle(MixedWork& w, hipStream_t s, bool y_is_zero, const s
     if ((e = launch_norm2_f64(D, B, w.dr.p, w.part.p, kNblk, !w.split, w.nrm.p, st)) != hipSuccess) return e;
     if ((e = launch_scale_d2f(D, B, w.nrm.p, w.dr.p, w.V.p, w.scl.p, st)) != hipSuccess) return e;
     ArnoldiArgs aa{R,         nch,     B,      m,    0,          L->d_rowptr.p, L->d_col.p, L->d_val32.p,
-                   spmv_order(L), w.V.p, DB,    w.scl.p, w.H.p, w.part.p, kNblk, pk_view(L, w.spmm_cols, true), w.split};
+                   spmv_order(L), w.V.p, DB,    w.scl.p, w.H.p, w.part.p, kNblk, pk_view(L, w.spmm_cols), w.split};
     RotArgsMixed rm{M, N, nch, B, L->d_Ob.p, L->d_Wb.p, w.split, L->d_wave.p, w.dG32.p, nullptr};
     for (int j = 0; j < m; ++j) {
       aa.j = j;
@@ -293,7 +293,7 @@ wp_status wpcd::solve_mixed(wp_lattice* L, const std::vector<double>& Elab, cons
   HIPCHECK(launch_init_rhs64(M, N, nch, B, L->d_W.p, L->d_wave.p, w.dj0.p, dg0.p, w.ds64.p, s));
   WP_LAUNCH("spmv_f32v_f64x", s,
             launch_spmv_f32v_f64x(R, nch, B, L->d_rowptr.p, L->d_col.p, L->d_val32.p, w.ds64.p, w.db.p, s, 0, -1,
-                                  spmv_order(L), pk_view(L, w.spmm_cols, !w.split)));
+                                  spmv_order(L), pk_view(L, w.spmm_cols)));
   HIPCHECK(launch_fill0(w.dy.p, DB, s));
   std::vector<MixedCol> col(B);
   std::vector<char> active(B, 1);

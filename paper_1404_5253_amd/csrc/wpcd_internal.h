@@ -246,30 +246,28 @@ hipError_t launch_init_rhs64(int M, int N, int nch, int B, const double* W, cons
                              int cb1 = -1);
 hipError_t launch_fill0(double2* p, int64_t n, hipStream_t st);
 // Device view of the packed block storage (many channels, PackDesc): npk values per block;
-// pkt[4 nc] = perm, lo, hi, off; spmm_min: wp_solve_opts.spmm_cols (0: the window of columns a
-// wavefront takes follows the column count).
+// pkt[4 nc] = perm, lo, hi, off; spmm_min: wp_solve_opts.spmm_cols; blocks: stored blocks of the resident P0.
 struct PackView {
   int npk = 0;
   const int* pkt = nullptr;
   int spmm_min = 0;
-  int64_t blocks = 0;   // stored blocks of the resident P0
-  // one order of summation per column count: the FP32 products of the refinement, whose operands are then
-  // rounded to BF16 (or BF16 pairs). Another order of the sums rounds some of them to the other neighbour, and
-  // a column then stops elsewhere, now and then a cycle earlier: solves that stop at an estimate of 1e-10
-  // differed by up to 1.5e-9 (unsplit) and 7e-9 (split, 8 in 300), with one order by 1e-10 at most. Also the
-  // residuals of the unsplit mode.
-  bool one_order = false;
+  int64_t blocks = 0;
 };
+// The order by slots in which a many-channel product of few columns adds the blocks of a row: block e goes into
+// partial sum e mod pk_slots(nc), and those are added one after another (k_spmv_pk: pk_rows rows per lane, as
+// many blocks at a time as the lanes hold).
+constexpr int pk_rows(int nc) { return nc % 2 == 0 ? 2 : 1; }
+constexpr int pk_slots(int nc) { return 64 / (nc / pk_rows(nc)); }
 // Many channels (spmm_mfma.h).
 hipError_t launch_spmm_pk(int64_t rows, int nch, int B, const int64_t* rowptr, const int32_t* col, const double* val,
                           const double2* x, double2* y, hipStream_t s, int cb0, int cb1, const int32_t* order,
-                          const PackView& pk);
+                          const PackView& pk, bool blockwise);
 hipError_t launch_spmm_pk(int64_t rows, int nch, int B, const int64_t* rowptr, const int32_t* col, const float* val,
                           const float2* x, float2* y, hipStream_t s, int cb0, int cb1, const int32_t* order,
-                          const PackView& pk);
+                          const PackView& pk, bool blockwise);
 hipError_t launch_spmm_pk(int64_t rows, int nch, int B, const int64_t* rowptr, const int32_t* col, const float* val,
                           const double2* x, double2* y, hipStream_t s, int cb0, int cb1, const int32_t* order,
-                          const PackView& pk);
+                          const PackView& pk, bool blockwise);
 // Block-CSR products for any storage/vector precision. Few channels (<= 4): full column-major
 // blocks, lanes over columns when B >= 16, else lanes over blocks with a wave reduction; many
 // channels: the packed blocks described by pk.

@@ -151,8 +151,8 @@ struct wp_lattice {
   DBuf<int> d_fkey, d_fcptr, d_fcm;
   DBuf<double> d_fcv;
 };
-inline PackView pk_view(const wp_lattice* L, int spmm_cols = 0, bool one_order = false) {
-  return PackView{L->pk.npk, L->d_pkt.p, std::max(0, spmm_cols), L->blocks, one_order};
+inline PackView pk_view(const wp_lattice* L, int spmm_cols = 0) {
+  return PackView{L->pk.npk, L->d_pkt.p, std::max(0, spmm_cols), L->blocks};
 }
 
 struct EnergyResult {
