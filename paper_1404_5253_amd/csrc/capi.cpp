@@ -462,6 +462,8 @@ extern "C" wp_status twobody_pseudostates(wp_lattice* L, const wp_potential_desc
     if (L->opens.empty() || L->opens.size() > 4) return fail(WP_EINVAL, "1..4 open deuteron channels required");
     L->d_O.reset();
     L->d_W.reset();
+    L->d_Of.reset();
+    L->d_Wf.reset();
     L->d_wave.reset();
     L->d_Ob.reset();
     L->d_Wb.reset();
@@ -1153,7 +1155,7 @@ static wp_status solve_fp64(wp_lattice* L, const std::vector<double>& Elab, cons
     if (use_graph && T == chunk) {
       const std::vector<int64_t> key{slot, M, N, nch, B, nfin, chunk, o.step_tile, o.spmm_cols,
                                      (int64_t)dG.p, (int64_t)dy.p, (int64_t)ds.p, (int64_t)dj0, (int64_t)pin, (int64_t)L->d_O.p, (int64_t)L->d_W.p,
-                                     (int64_t)L->d_wave.p, (int64_t)L->d_rowptr.p, (int64_t)L->d_col.p,
+                                     (int64_t)L->d_Of.p, (int64_t)L->d_Wf.p, (int64_t)L->d_wave.p, (int64_t)L->d_rowptr.p, (int64_t)L->d_col.p,
                                      (int64_t)val, (int64_t)order, (int64_t)L->d_pkt.p, L->blocks};
       HIPCHECK(graph_run(L, ws.chunk_graph[slot], key, s, [&](hipStream_t st) { return record_chunk(st, slot, T); }));
     } else {

@@ -171,7 +171,7 @@ wp_status wpcd::mixed_cycle(MixedWork& w, hipStream_t s, bool y_is_zero, const s
         (int64_t)w.dy.p,    (int64_t)w.ds64.p, (int64_t)w.dKy.p, (int64_t)w.dG64.p, (int64_t)w.dG32.p,
         (int64_t)w.dj0.p,   (int64_t)w.dfin.p, (int64_t)w.part.p, (int64_t)w.nrm.p, (int64_t)w.V.p,
         (int64_t)w.scl.p,   (int64_t)w.H.p, (int64_t)w.t32.p, (int64_t)w.kv32.p, (int64_t)L->d_O.p,
-        (int64_t)L->d_W.p,  (int64_t)L->d_wave.p, (int64_t)L->d_Ob.p, (int64_t)L->d_Wb.p,
+        (int64_t)L->d_W.p,  (int64_t)L->d_Of.p, (int64_t)L->d_Wf.p, (int64_t)L->d_wave.p, (int64_t)L->d_Ob.p, (int64_t)L->d_Wb.p,
         (int64_t)L->d_rowptr.p, (int64_t)L->d_col.p, (int64_t)L->d_val32.p,
         (int64_t)spmv_order(L), (int64_t)L->d_pkt.p, L->blocks};
     HIPCHECK(graph_run(L, w.sweep_graph[y_is_zero ? 0 : 1], key, s, record_sweep));
