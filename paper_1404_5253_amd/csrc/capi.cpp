@@ -478,9 +478,8 @@ extern "C" wp_status twobody_pseudostates(wp_lattice* L, const wp_potential_desc
 
 static wp_status upload_tables(wp_lattice* L);
 
-// device copies of O and W of every pair wave and the channel -> wave map (first GPU use)
-wp_status wpcd::upload_waves(wp_lattice* L) {
-  if (L->d_O.p) return WP_OK;
+// device copies of O and W of every pair wave, the channel -> wave map and the G1 tables (first GPU use)
+static wp_status make_waves(wp_lattice* L) {
   const size_t MM = (size_t)L->M * L->M;
   std::vector<double> O(MM * L->waves.size()), W(MM * L->waves.size());
   for (size_t k = 0; k < L->waves.size(); ++k) {
@@ -535,6 +534,17 @@ wp_status wpcd::upload_waves(wp_lattice* L) {
   HIPCHECK(hipMemcpy(L->d_gl_x.p, glx.data(), 36 * 8, hipMemcpyHostToDevice));
   HIPCHECK(hipMemcpy(L->d_gl_w.p, glw.data(), 36 * 8, hipMemcpyHostToDevice));
   return WP_OK;
+}
+
+// d_O stands for all of these tables, so it stays only if they are complete
+wp_status wpcd::upload_waves(wp_lattice* L) {
+  if (L->d_O.p) return WP_OK;
+  const wp_status st = make_waves(L);
+  if (st != WP_OK) {
+    (void)hipStreamSynchronize(nullptr);   // a packing kernel may be reading it
+    L->d_O.reset();
+  }
+  return st;
 }
 
 bool wpcd::g1_work(wp_lattice* L, int nE, DBuf<int64_t>& w) {
@@ -619,8 +629,7 @@ extern "C" wp_status wp_lattice_resolvent(const wp_lattice* Lc, double E_lab, in
 
 // ------------------------------------------------------------------ P0 build
 
-static wp_status upload_tables(wp_lattice* L) {
-  if (L->d_pe.p) return WP_OK;
+static wp_status make_tables(wp_lattice* L) {
   std::vector<double> gx(L->n_x), gwx(L->n_x), gp(L->n_phi), gwp(L->n_phi);
   gauss_legendre(L->n_x, gx.data(), gwx.data());
   gauss_legendre(L->n_phi, gp.data(), gwp.data());
@@ -709,6 +718,14 @@ static wp_status upload_tables(wp_lattice* L) {
     fz.cv = L->d_fcv.p;
   }
   return WP_OK;
+}
+
+// d_pe stands for all of these tables, so it stays only if they are complete
+static wp_status upload_tables(wp_lattice* L) {
+  if (L->d_pe.p) return WP_OK;
+  const wp_status st = make_tables(L);
+  if (st != WP_OK) L->d_pe.reset();
+  return st;
 }
 
 // Sub-allocations of one device buffer (256-byte aligned); with base = nullptr it only sizes.

@@ -25,15 +25,24 @@
 
 using namespace wpcd;
 
+static wp_status make_bf16(wp_lattice* L, hipStream_t s) {
+  const int nw = (int)L->waves.size();
+  const size_t n = frag_bf16_elems(L->M) * nw;
+  if (!L->d_Wb.make(&L->al, n) || !L->d_Ob.make(&L->al, n)) return fail(WP_ENOMEM, "device allocation (bf16 blocks)");
+  HIPCHECK(launch_pack_bf16(L->M, nw, L->d_O.p, L->d_Ob.p, s));
+  HIPCHECK(launch_pack_bf16(L->M, nw, L->d_W.p, L->d_Wb.p, s));
+  HIPCHECK(hipStreamSynchronize(s));   // ready for later calls, on any stream
+  return WP_OK;
+}
+
 wp_status wpcd::ensure_mixed(wp_lattice* L, hipStream_t s) {
   if (wp_status st = upload_waves(L)) return st;
-  if (!L->d_Ob.p) {
-    const int nw = (int)L->waves.size();
-    const size_t n = frag_bf16_elems(L->M) * nw;
-    if (!L->d_Wb.make(&L->al, n) || !L->d_Ob.make(&L->al, n)) return fail(WP_ENOMEM, "device allocation (bf16 blocks)");
-    HIPCHECK(launch_pack_bf16(L->M, nw, L->d_O.p, L->d_Ob.p, s));
-    HIPCHECK(launch_pack_bf16(L->M, nw, L->d_W.p, L->d_Wb.p, s));
-    HIPCHECK(hipStreamSynchronize(s));   // ready for later calls, on any stream
+  if (!L->d_Ob.p) {   // d_Ob stands for both tables
+    if (wp_status st = make_bf16(L, s)) {
+      (void)hipStreamSynchronize(s);
+      L->d_Ob.reset();
+      return st;
+    }
   }
   if (!L->d_val32.p) {
     const int64_t n = L->blocks * L->vpb;
