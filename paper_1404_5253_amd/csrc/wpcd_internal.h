@@ -100,9 +100,9 @@ struct DBuf {
   bool make(DevAlloc* a, size_t count) {
     reset();
     al = a;
-    n = count;
     if (count == 0) return true;
     p = static_cast<T*>(a->alloc(count * sizeof(T)));
+    if (p) n = count;   // n is the room there is: 0 after a refused allocation
     return p != nullptr;
   }
   ~DBuf() { reset(); }

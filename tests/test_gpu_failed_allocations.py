@@ -84,3 +84,14 @@ def test_call_after_a_refused_allocation(monkeypatch, channels, call):
         L.build_perm("fp64")
         return L
     assert refuse_each(monkeypatch, make, CALLS[call]) > 10
+
+
+def build(L, precision="fp64"):
+    L.build_perm(precision)
+    rp, col, val = L.export_perm()
+    return np.concatenate([rp, col, val.ravel()])
+
+
+@pytest.mark.parametrize("channels", ["doublet", "pw10"])   # both kinds of build: candidate values, fused
+def test_build_after_a_refused_allocation(monkeypatch, channels):
+    assert refuse_each(monkeypatch, lambda: lattice(channels), build) > 10
