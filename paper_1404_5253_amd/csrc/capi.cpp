@@ -798,6 +798,7 @@ extern "C" wp_status perm_matrix_build(wp_lattice* L, int precision, void* strea
     if (!L->d_rowptr.make(&L->al, R + 1)) return fail(WP_ENOMEM, "device allocation (row pointer)");
   }
   if (!L->h_tot) HIPCHECK(hipHostMalloc((void**)&L->h_tot, 2 * sizeof(int64_t)));
+  L->have_P = false;   // from here to the end of the build no P0 is complete
   // the other precision's copy, derived from the previous P0, is dropped
   if (precision == WP_P_FP64) L->d_val32.reset();
   else L->d_val64.reset();

@@ -95,3 +95,22 @@ def build(L, precision="fp64"):
 @pytest.mark.parametrize("channels", ["doublet", "pw10"])   # both kinds of build: candidate values, fused
 def test_build_after_a_refused_allocation(monkeypatch, channels):
     assert refuse_each(monkeypatch, lambda: lattice(channels), build) > 10
+
+
+@pytest.mark.parametrize("channels", ["doublet", "pw10"])
+def test_no_solve_on_a_failed_rebuild(monkeypatch, channels):
+    alloc = Refusing()
+    monkeypatch.setattr(wp, "TorchAllocator", lambda: alloc)
+    L = lattice(channels)
+    L.build_perm("fp64")
+    expected = solve(L, "fp64")
+    alloc.refuse = 0   # the FP32 values, whose build drops the FP64 ones
+    with pytest.raises(wp.WpError) as e:
+        L.build_perm("fp32")
+    assert e.value.status == wp.WP_ENOMEM
+    for mode in ("fp64", "mixed_split"):
+        with pytest.raises(wp.WpError) as e:
+            solve(L, mode)
+        assert e.value.status == wp.WP_ENOTREADY, mode
+    L.build_perm("fp64")
+    assert np.array_equal(solve(L, "fp64"), expected)
