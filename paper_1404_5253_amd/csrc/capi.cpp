@@ -764,7 +764,7 @@ extern "C" wp_status perm_matrix_build(wp_lattice* L, int precision, void* strea
   // node tables of every q-box in HBM, shared by selection and quadrature, when the moment count
   // allows it (weights padded to AS entries per node)
   const int nn = L->n_x * L->n_phi, nmom = (int)L->keys.size();
-  const bool use_tab = nmom <= 4 && nn <= 128 && 9 * M + 1 <= 8192;
+  const bool use_tab = node_tables_fit(a);
   const int AS = ((nmom <= 1 ? 1 : nmom <= 2 ? 2 : 4) + 2) & ~1;
   double *geo = nullptr, *aux = nullptr, *fgeo = nullptr;
   const bool fused = L->keys.size() > 8 && L->fz_ok;

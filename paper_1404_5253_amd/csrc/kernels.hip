@@ -333,14 +333,24 @@ __global__ void __launch_bounds__(64 * BPW) k_select_tab(PBuildArgs a, const dou
   }
 }
 
+// What the two kernels that read the node tables take: up to 128 nodes and 4 moments, and in 64 KB of LDS the p edges
+// and two bounds per row for each box of the selection (the smaller room: up to 910 rows), or the coefficients, the
+// p edges and the row lists of the quadrature (k_pbuild_tab).
+constexpr int PT_ROWS = 128;   // rows of a list
+static size_t select_tab_lds(const PBuildArgs& a) { return (size_t)(a.M + 1 + BPW * 2 * a.M) * sizeof(double); }
+static size_t pbuild_tab_lds(const PBuildArgs& a) { return (size_t)(a.nch * a.nch * a.nmom + a.M + 1) * sizeof(double); }
+bool node_tables_fit(const PBuildArgs& a) {
+  const int nn = a.n_x * a.n_phi;
+  const size_t lists = BPW * PT_ROWS * (sizeof(int64_t) + 3 * sizeof(int));
+  return a.nch >= 1 && a.nmom >= 1 && a.nmom <= 4 && nn >= 1 && nn <= 128 && a.M >= 1 && a.M <= 1024 && a.N >= 1 &&
+         a.N <= 1024 && select_tab_lds(a) <= 64 * 1024 && lists + pbuild_tab_lds(a) <= 64 * 1024;
+}
+
 hipError_t launch_select_tab(const PBuildArgs& a, const double* geo, const double* aux, int AS, int2* hull, int* cnt,
                              int* lo, hipStream_t s) {
-  const int nn = a.n_x * a.n_phi;
-  if (nn < 1 || nn > 128 || a.M < 1 || a.M > 1024 || a.N < 1 || a.N > 1024) return hipErrorInvalidValue;
-  const size_t sh = (size_t)(a.M + 1 + BPW * 2 * a.M) * sizeof(double);
-  if (sh > 64 * 1024) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_select_tab, dim3((a.N * a.N + BPW - 1) / BPW), dim3(64 * BPW), sh, s, a, geo, aux, AS, hull, cnt,
-                     lo);
+  if (!node_tables_fit(a)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_select_tab, dim3((a.N * a.N + BPW - 1) / BPW), dim3(64 * BPW), select_tab_lds(a), s, a, geo, aux,
+                     AS, hull, cnt, lo);
   return hipGetLastError();
 }
 
@@ -763,7 +773,7 @@ __global__ void __launch_bounds__(64 * BPW) k_pbuild_tab(PBuildArgs a, const dou
                                                          const int64_t* __restrict__ rowptr_c,
                                                          int32_t* __restrict__ col_c, double* __restrict__ val_c,
                                                          uint8_t* __restrict__ flag, int64_t cap) {
-  constexpr int ROWS = 128;
+  constexpr int ROWS = PT_ROWS;
   __shared__ int64_t s_base_[BPW][ROWS];   // block of candidate e of a listed row = base + e
   __shared__ int s_pref_[BPW][ROWS];       // candidates of the listed rows before it
   __shared__ int s_row_[BPW][ROWS];        // row i
@@ -881,13 +891,8 @@ __global__ void __launch_bounds__(64 * BPW) k_pbuild_tab(PBuildArgs a, const dou
 hipError_t launch_pbuild_tab(const PBuildArgs& a, const double* geo, const double* aux, int AS, const int2* hull,
                              const int* cnt, const int* lo, const int* segoff, const int64_t* rowptr_c, int32_t* col_c,
                              double* val_c, uint8_t* flag, int64_t cap, hipStream_t s) {
-  if (a.nmom < 1 || a.nmom > 4 || AS < 1 + a.nmom || a.nch < 1) return hipErrorInvalidValue;
-  const int nn = a.n_x * a.n_phi;
-  // the sizes taken: coefficients, p edges and, BPW times, one node table and M row entries in 64 KB
-  const size_t per_box = ((size_t)nn * (4 + AS) * sizeof(double) + (size_t)a.M * sizeof(int64_t) +
-                          (2 * a.M + 1) * sizeof(int) + 7) & ~(size_t)7;
-  const size_t sh = (size_t)(a.nch * a.nch * a.nmom + a.M + 1) * sizeof(double);
-  if (sh + BPW * per_box > 64 * 1024) return hipErrorInvalidValue;
+  if (!node_tables_fit(a) || AS < 1 + a.nmom) return hipErrorInvalidValue;
+  const size_t sh = pbuild_tab_lds(a);
   dim3 g((a.N * a.N + BPW - 1) / BPW), b(64 * BPW);
 #define WP_TAB(NM, EW) \
   hipLaunchKernelGGL((k_pbuild_tab<NM, EW>), g, b, sh, s, a, geo, aux, AS, hull, cnt, lo, segoff, rowptr_c, col_c, val_c, \

@@ -161,6 +161,7 @@ hipError_t launch_scan(const int64_t* in, int64_t* out, int64_t n, int64_t* tmp,
 // Node tables of all q-boxes: geo[box][nd] = (r1, r2, Q1, Q2), aux[box] = AS rows of nodes:
 // z1, w_0 .. w_{nmom-1}, zeros; selection and quadrature reading them. hull[box] = the rows [x, y) of a box that
 // can have candidates; cnt, lo, segoff hold only those.
+bool node_tables_fit(const PBuildArgs& a);   // else launch_select and launch_pbuild
 hipError_t launch_node_table(const PBuildArgs& a, double* geo, double* aux, int AS, hipStream_t s);
 hipError_t launch_select_tab(const PBuildArgs& a, const double* geo, const double* aux, int AS, int2* hull, int* cnt,
                              int* lo, hipStream_t s);
