@@ -1903,7 +1903,9 @@ hipError_t launch_step64(const RotArgs& r, const double* W, const double2* y, do
   // column 7.7 / 8.5 / 11, 4 columns 10.5 / 9.6 / 11.9, 16 columns 26 / 21 / 18.6; 1 channel, M = N = 400,
   // 1 column 32 / 38 / 60, 2 columns 56 / 40 / 60; 18 channels, M = N = 150, 4 columns 143 / 97 / 79
   // (16 columns per workgroup: 85). More than 512 rows: 8 columns need more registers than there are.
-  const int dflt = wgs(8) >= 240 && nt <= 32 ? 8 : wgs(4) >= 200 ? 4 : 2;
+  // The two kinds of kernel fuse different products of G1 t (step_scale), which the Pade sums of a divergent series
+  // carry into the amplitude, so the line of 256 workgroups between them also decides last bits and stays where it is.
+  const int dflt = wgs(8) >= 256 && nt <= 32 ? 8 : wgs(4) >= 200 ? 4 : 2;
   // an explicit choice (WP_STEP_*) that fits the lattice replaces the choice by grid size
   const int cc = r.tile == WP_STEP_MFMA16 && nt <= 16 ? 16
                  : r.tile == WP_STEP_MFMA8 && nt <= 32 ? 8
