@@ -538,6 +538,7 @@ static wp_status make_waves(wp_lattice* L) {
 
 // d_O stands for all of these tables, so it stays only if they are complete
 wp_status wpcd::upload_waves(wp_lattice* L) {
+  std::lock_guard<std::mutex> lk(L->tables_mu);
   if (L->d_O.p) return WP_OK;
   const wp_status st = make_waves(L);
   if (st != WP_OK) {
@@ -722,6 +723,7 @@ static wp_status make_tables(wp_lattice* L) {
 
 // d_pe stands for all of these tables, so it stays only if they are complete
 static wp_status upload_tables(wp_lattice* L) {
+  std::lock_guard<std::mutex> lk(L->tables_mu);
   if (L->d_pe.p) return WP_OK;
   const wp_status st = make_tables(L);
   if (st != WP_OK) L->d_pe.reset();

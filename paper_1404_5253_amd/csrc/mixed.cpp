@@ -35,8 +35,18 @@ static wp_status make_bf16(wp_lattice* L, hipStream_t s) {
   return WP_OK;
 }
 
+static wp_status make_val32(wp_lattice* L, hipStream_t s) {
+  const int64_t n = L->blocks * L->vpb;
+  if (!L->d_val32.make(&L->al, std::max<int64_t>(n, 1))) return fail(WP_ENOMEM, "device allocation (FP32 P0)");
+  if (n > 0) HIPCHECK(launch_cvt_scalar(n, L->d_val64.p, L->d_val32.p, s));
+  if (!L->val32_ev) HIPCHECK(hipEventCreateWithFlags(&L->val32_ev, hipEventDisableTiming));
+  HIPCHECK(hipEventRecord(L->val32_ev, s));
+  return WP_OK;
+}
+
 wp_status wpcd::ensure_mixed(wp_lattice* L, hipStream_t s) {
   if (wp_status st = upload_waves(L)) return st;
+  std::lock_guard<std::mutex> lk(L->mixed_mu);
   if (!L->d_Ob.p) {   // d_Ob stands for both tables
     if (wp_status st = make_bf16(L, s)) {
       (void)hipStreamSynchronize(s);
@@ -45,9 +55,13 @@ wp_status wpcd::ensure_mixed(wp_lattice* L, hipStream_t s) {
     }
   }
   if (!L->d_val32.p) {
-    const int64_t n = L->blocks * L->vpb;
-    if (!L->d_val32.make(&L->al, std::max<int64_t>(n, 1))) return fail(WP_ENOMEM, "device allocation (FP32 P0)");
-    if (n > 0) HIPCHECK(launch_cvt_scalar(n, L->d_val64.p, L->d_val32.p, s));
+    if (wp_status st = make_val32(L, s)) {
+      (void)hipStreamSynchronize(s);
+      L->d_val32.reset();
+      return st;
+    }
+  } else if (L->val32_ev) {   // a conversion on another stream may still run
+    HIPCHECK(hipStreamWaitEvent(s, L->val32_ev, 0));
   }
   return WP_OK;
 }

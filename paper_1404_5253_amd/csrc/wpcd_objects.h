@@ -105,6 +105,10 @@ struct wp_lattice {
   bool order_ok = false;   // d_order holds the order of the resident P0 (or it is enqueued)
   hipEvent_t order_ev = nullptr;   // recorded after the order kernel
   std::mutex order_mu;
+  // the first use of a table makes it, in whichever thread comes first: lattice, wave and G1 tables; BF16 tables and
+  // the FP32 copy of the resident P0 (recorded in val32_ev on the stream that converted it)
+  std::mutex tables_mu, mixed_mu;
+  hipEvent_t val32_ev = nullptr;
   DBuf<char> scratch_sel, scratch_cand;   // P0 build scratch kept between builds (grow-only)
   // Solve workspaces reused across calls (grow-only) by the call that holds ws_mu; a call that
   // finds it held (another thread on this lattice) allocates its own.
@@ -129,6 +133,7 @@ struct wp_lattice {
     if (pin) (void)hipHostFree(pin);
     if (h_tot) (void)hipHostFree(h_tot);
     if (order_ev) (void)hipEventDestroy(order_ev);
+    if (val32_ev) (void)hipEventDestroy(val32_ev);
     for (hipEvent_t e : build_ev)
       if (e) (void)hipEventDestroy(e);
     ws64.chunk_graph[0].reset();
