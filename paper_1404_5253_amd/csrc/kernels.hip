@@ -2095,8 +2095,9 @@ static void spmv_dispatch(int64_t rows, int B, int cb0, int cb1, const int64_t* 
   hipLaunchKernelGGL((k_spmv<VT, XT, AT, NC, CT, RT>), dim3((unsigned)((rows + 8 * RT - 1) / (8 * RT))), dim3(256), \
                      0, s, rows, B, cb0, cb1, rowptr, col, val, x, y, order)
     // 4 columns at a time (8 of them with 2 channels: 24 us in FP64, 29 with 8 at a time, too many registers);
-    // 8 with one channel unless 4 hold the rest (8 columns 13.6 us with 4, 14.4 with 8; 15 columns 19.3 and
-    // 17.5). Two rows at a time where rows are plenty: one column of one channel at 160000 rows 31.5 -> 28.9
+    // 8 with one channel from 13 columns on, where 4 at a time would take a fourth turn (us, 4 / 8 at a time, FP64:
+    // 8 columns 13.6 / 14.4 at 10000 rows, 104 / 113 at 160000; 12 columns 16.3 / 17.7 and 129 / 152; 15 columns
+    // 19.8 / 17.6 and 203 / 160; at 1600 rows 5 to 8 columns 7.2 / 7.2 at most). Two rows at a time where rows are plenty: one column of one channel at 160000 rows 31.5 -> 28.9
     // us, at 40000 rows 11.9 -> 11.4; with 2 channels slower (28 -> 36 us at 90000 rows).
     const bool deep = NC == 1 && rows >= 32768;
     if (nc == 1) {
@@ -2104,7 +2105,7 @@ static void spmv_dispatch(int64_t rows, int B, int cb0, int cb1, const int64_t* 
         if constexpr (NC == 1) WP_SPMV(1, 2);
       } else WP_SPMV(1, 1);
     } else if (nc == 2) WP_SPMV(2, 1);
-    else if (NC > 1 || nc <= 4 || (nc > 8 && nc <= 12)) WP_SPMV(4, 1);
+    else if (NC > 1 || nc <= 12) WP_SPMV(4, 1);
     else if constexpr (NC == 1) WP_SPMV(8, 1);
 #undef WP_SPMV
   }
