@@ -1899,13 +1899,16 @@ hipError_t launch_step64(const RotArgs& r, const double* W, const double2* y, do
   const int Mp = (r.M + 15) / 16 * 16, nt = Mp / 16;
   auto wgs = [&](int cc) { return (int64_t)((ncol + cc - 1) / cc) * r.nch; };
   // Complex columns per workgroup: every workgroup reads both tables, so the widest tile that still
-  // gives the compute units work. Measured (us, tiles of 2 / 4 / 8 columns): 2 channels, M = N = 100, 1
+  // gives the compute units work: of 2 columns while each compute unit gets one workgroup at most, a second round of
+  // them costs more than the wider tile. Measured (us, tiles of 2 / 4 / 8 columns): 2 channels, M = N = 100, 1
   // column 7.7 / 8.5 / 11, 4 columns 10.5 / 9.6 / 11.9, 16 columns 26 / 21 / 18.6; 1 channel, M = N = 400,
-  // 1 column 32 / 38 / 60, 2 columns 56 / 40 / 60; 18 channels, M = N = 150, 4 columns 143 / 97 / 79
+  // 1 column 32 / 38 / 60, 2 columns 56 / 40 / 60. At 240, 250, 260 and 300 workgroups of 2 columns: 32 / 37 (1
+  // channel, M = 400, N = 240), 17.8 / 18.8 (1 channel, 250), 21 / 16 (2 channels, M = 200, N = 130) and 16 / 12.5
+  // (2 channels, 150), 54 / 38 (1 channel, M = 400, N = 300). 18 channels, M = N = 150, 4 columns 143 / 97 / 79
   // (16 columns per workgroup: 85). More than 512 rows: 8 columns need more registers than there are.
   // The two kinds of kernel fuse different products of G1 t (step_scale), which the Pade sums of a divergent series
   // carry into the amplitude, so the line of 256 workgroups between them also decides last bits and stays where it is.
-  const int dflt = wgs(8) >= 256 && nt <= 32 ? 8 : wgs(4) >= 200 ? 4 : 2;
+  const int dflt = wgs(8) >= 256 && nt <= 32 ? 8 : wgs(2) > 256 ? 4 : 2;
   // an explicit choice (WP_STEP_*) that fits the lattice replaces the choice by grid size
   const int cc = r.tile == WP_STEP_MFMA16 && nt <= 16 ? 16
                  : r.tile == WP_STEP_MFMA8 && nt <= 32 ? 8
