@@ -1875,11 +1875,7 @@ hipError_t launch_pack_frag(int M, int nw, const double* A, double2* F, hipStrea
 template <typename K>
 static hipError_t launch_step_k(K kern, const RotArgs& r, const double2* y, double2* s_out, int Mp, int cc, int tpw,
                                 hipStream_t s) {
-  const size_t lds = (size_t)Mp * 2 * cc * sizeof(double);
-  if (lds > 64 * 1024 &&
-      hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
-          hipSuccess)
-    return hipErrorInvalidValue;
+  const size_t lds = (size_t)Mp * 2 * cc * sizeof(double);   // 64 KB at most (launch_step64)
   const int nt = Mp / 16, nw = (nt + tpw - 1) / tpw;
   const dim3 grid((r.N * r.B + cc - 1) / cc, r.nch);
   hipLaunchKernelGGL(kern, grid, dim3(64 * nw), lds, s, r, y, s_out, Mp);

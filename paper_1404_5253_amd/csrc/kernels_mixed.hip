@@ -295,7 +295,8 @@ static hipError_t launch_step_bf16_ct(const RotArgsMixed& r, const float2* y, fl
   const int nt = (r.M + 15) / 16, ns = (r.M + 31) / 32;
   if (nt <= 16) return launch_step_bf16_k<SPLIT, CT, 1, 4>(r, y, s_out, nt, ns, s);
   if (nt <= 32) return launch_step_bf16_k<SPLIT, CT, 2, 2>(r, y, s_out, nt, ns, s);
-  return launch_step_bf16_k<SPLIT, 1, 4, 2>(r, y, s_out, nt, ns, s);
+  if constexpr (SPLIT) return hipErrorInvalidValue;   // more than 512 rows
+  else return launch_step_bf16_k<false, 1, 4, 2>(r, y, s_out, nt, ns, s);
 }
 
 hipError_t launch_step_bf16(const RotArgsMixed& r, const float2* y, float2* s_out, hipStream_t s) {
