@@ -304,9 +304,9 @@ hipError_t launch_step_bf16(const RotArgsMixed& r, const float2* y, float2* s_ou
   if (r.M < 1 || r.M > (r.split ? 512 : 1024) || r.N < 1 || r.B < 1 || r.nch < 1 || !r.G || !r.Of || !r.Wf)
     return hipErrorInvalidValue;
   // 16 columns per workgroup read the tables half as often as 8, which wins once the row tiles of all
-  // workgroups fill the device (us, 8 / 16 columns, split): 2 channels, M = N = 100, 8 columns 8.5 / 9.9,
-  // 64 columns 24.5 / 20.4; 18 channels, M = N = 150, 4 columns 36 / 28.5; 1 channel, M = 400, N = 300,
-  // 4 columns 20.7 / 24.8, 8 columns 35 / 25
+  // workgroups fill the device (us, 8 / 16 columns, split): 2 channels, M = N = 100, 8 columns 8.7 / 10.1,
+  // 16 columns (1400 row tiles) 10.9 / 10.5, 32 columns (2800) 16.0 / 12.8, 64 columns 24.6 / 20.2; 18 channels,
+  // M = N = 150, 4 columns 37 / 30; 1 channel, M = 400, N = 300, 4 columns (1875) 22 / 29, 8 columns 38 / 30
   const bool wide = (int64_t)((r.N * r.B + 15) / 16) * r.nch * ((r.M + 15) / 16) >= 2400;
   if (r.split) return wide ? launch_step_bf16_ct<true, 2>(r, y, s_out, s) : launch_step_bf16_ct<true, 1>(r, y, s_out, s);
   return wide ? launch_step_bf16_ct<false, 2>(r, y, s_out, s) : launch_step_bf16_ct<false, 1>(r, y, s_out, s);

@@ -271,7 +271,7 @@ hipError_t launch_spmm_pk(int64_t rows, int nch, int B, const int64_t* rowptr, c
                           const PackView& pk, bool blockwise);
 // Block-CSR products for any storage/vector precision. Few channels (<= 4): full column-major
 // blocks, lanes over columns when B >= 16, else lanes over blocks with a wave reduction; many
-// channels: the packed blocks described by pk.
+// channels: the packed blocks described by pk, passes of up to 4 columns or the matrix cores.
 // order: the block rows in the sequence the wavefronts take them (longest first), or nullptr
 hipError_t launch_spmv_f64(int64_t rows, int nch, int B, const int64_t* rowptr, const int32_t* col, const double* val,
                            const double2* x, double2* y, hipStream_t s, int cb0, int cb1, const int32_t* order,

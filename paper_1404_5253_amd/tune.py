@@ -9,8 +9,8 @@ the chosen configuration below the target on other draws of energies.
 A second stage tunes how the chosen configuration is launched, one choice at a time (each kept
 only if it is faster and still within the margin): the FP64 step kernel (`step_tile`: MFMA with
 8, 16 or 2 ("rows") columns per workgroup, or the VALU kernel), with more than
-4 channels the column count from which the block-CSR products run lanes over the columns
-(`spmm_cols`), HIP-graph replay of the term chunks / Arnoldi sweeps (`graph`), and the batch
+4 channels the column count from which the block-CSR products add a row's blocks one after another
+and below which they take passes of 4 columns (`spmm_cols`), HIP-graph replay of the term chunks / Arnoldi sweeps (`graph`), and the batch
 width (energies per call; the batch is solved in calls of that many energies).
 """
 from __future__ import annotations
@@ -22,7 +22,7 @@ import numpy as np
 TOL_LADDER = (1e-4, 3e-5, 1e-5, 3e-6, 1e-6, 3e-7, 1e-7, 3e-8, 1e-8, 3e-9, 1e-9)
 CYCLES = (6, 8, 10, 12)
 STEP_TILES = ("auto", "mfma8", "mfma16", "rows", "valu")
-SPMM_COLS = (0, 8, 32, 1 << 20)          # 0: the library's default (16); 1 << 20: never
+SPMM_COLS = (0, 8, 32, 1 << 20)          # 0: 16, and FP64 vectors below it on the matrix cores; 1 << 20: passes of 4 always
 WIDTH_DIVISORS = (1, 2, 4)
 LAUNCH_DEFAULTS = dict(step_tile="auto", spmm_cols=0, graph=False, width=None)
 

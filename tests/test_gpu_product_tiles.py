@@ -1,8 +1,8 @@
-"""The few-channel products of 16 and more columns (tiles of 16 columns and 16 rows, 4 or 8 blocks of a row a
-turn), plain and with the Arnoldi sums: column counts around the tiles, rows around the workgroups, one and two
-channels, short and long Arnoldi cycles. FP64 series terms column by column against one energy at a time at
-the tolerance of tests/parity_util.py; refinement amplitudes, whose FP64 residual decides when a column is
-done, against one energy at a time at 1e-8."""
+"""The few-channel products of 16 and more columns (tiles of 16 columns and 16 rows, 8 blocks of a row a turn),
+plain and with the Arnoldi sums of the default cycle (other cycles and 4 blocks a turn: test_gpu_arnoldi_cycles):
+column counts around the tiles, rows around the workgroups, one and two channels. FP64 series terms column by
+column against one energy at a time at the tolerance of tests/parity_util.py; refinement amplitudes, whose FP64
+residual decides when a column is done, against one energy at a time at 1e-8."""
 import numpy as np
 import pytest
 

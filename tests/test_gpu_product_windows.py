@@ -1,5 +1,5 @@
 """The many-channel block-CSR products at the edges of their column windows (spmm_mfma.h): windows of
-4, 8, 16 and 32 columns, full, partly filled and repeated, one and four wavefronts per block row.
+4, 8, 16 and 32 columns, full, partly filled and repeated, one wavefront and several per block row.
 
 FP64 series terms against the oracle at the tolerance of tests/parity_util.py; lattices of more than
 16384 rows against the passes of 4 columns (spmm_cols above the column count), which the oracle

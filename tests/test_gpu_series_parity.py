@@ -12,18 +12,20 @@ The solve kernels are chosen by the grid a call makes (columns = energies x open
 
 | case | columns | FP64 step | SpMV / SpMM |
 |---|---|---|---|
-| doublet_mt_20, 1 energy | 1 | k_step64r (MFMA, all row tiles per workgroup) | k_spmv, 2 channels |
-| doublet_mt_20, 64 energies | 64 | k_step64m<1> (MFMA, >= 256 workgroups) | k_spmm, 2 channels |
-| pw18_mt_6, 1 energy | 2 | k_step64r | k_spmv_pk<18, 2 columns> |
-| pw18_mt_6, 2 energies | 4 | k_step64r | k_spmv_pk<18, 4 columns> |
-| pw18_mt_6, 20 energies | 40 | k_step64m<2> | k_spmm_pk |
-| pw10_mt_8, 2 energies | 4 | k_step64r | k_spmv_pk<10, 4 columns> |
-| doublet_mt_136x8, 1 energy | 1 | k_step64 (VALU, M > 128) | k_spmv, 2 channels |
-| quartet_yam_24, 3 energies | 3 | k_step64r | k_spmv, 1 channel |
-| pw30_mt_4, 3 and 12 energies | 3 x open channels | k_step64r / k_step64m | k_spmv_pk<30, 4> (more than 24 channels) |
+| doublet_mt_20, 1 energy | 1 | k_step64q<1> (2 columns per workgroup) | k_spmv, 2 channels |
+| doublet_mt_20, 64 energies | 64 | k_step64m<1> (8 columns, >= 256 workgroups) | k_spmm, 2 channels |
+| pw18_mt_6, 1 energy | 2 | k_step64q<1> | k_spmm_f64<18> by slots, 4 columns |
+| pw18_mt_6, 2 energies | 4 | k_step64q<1> | k_spmm_f64<18> by slots, 4 columns |
+| pw18_mt_6, 20 energies | 40 | k_step64m<1> | k_spmm_f64<18> block after block, 32 columns |
+| pw10_mt_8, 2 energies | 4 | k_step64q<1> | k_spmm_f64<10> by slots, 4 columns |
+| doublet_mt_136x8, 1 energy | 1 | k_step64q<1> (9 row tiles) | k_spmv, 2 channels |
+| quartet_yam_24, 3 energies | 3 | k_step64q<1> | k_spmv, 1 channel |
+| pw30_mt_4, 3 and 12 energies | 3 x open channels | k_step64q<2> / k_step64m<1> | k_spmm_f64<30> by slots, 8 columns |
 
+k_spmv_pk on FP64 vectors (one, two or four columns of a P0 above 800 MB, and on request) adds in the order of the
+products by slots: test_gpu_product_order compares the two bit for bit, so these cases pin both.
 Many-channel P0 (more than 4 channels) is stored packed: only the channel pairs with a nonzero
-recoupling coefficient, in a permuted channel order (k_spmv_pk, k_spmm_pk).
+recoupling coefficient, in a permuted channel order (k_spmv_pk, k_spmm_f32, k_spmm_f64).
 """
 import numpy as np
 import pytest
