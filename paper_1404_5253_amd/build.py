@@ -21,6 +21,12 @@ def hipcc() -> str:
     return "hipcc"
 
 
+def _jobs() -> int:
+    """Compilers at a time: MAX_JOBS where it is a positive number, else 8."""
+    n = os.environ.get("MAX_JOBS", "").strip()
+    return int(n) if n.isdigit() and int(n) > 0 else 8
+
+
 def _run(cmds, over, verbose):
     if verbose:
         for c in cmds:
@@ -41,7 +47,7 @@ def build(verbose: bool = False) -> str:
     with tempfile.TemporaryDirectory() as work:
         objs = [os.path.join(work, os.path.basename(s) + ".o") for s in srcs]
         cmds = [cc + ["-c", s, "-o", o] for s, o in zip(srcs, objs)]
-        with ThreadPoolExecutor(int(os.environ.get("MAX_JOBS", "8"))) as pool:
+        with ThreadPoolExecutor(_jobs()) as pool:
             _run(cmds, pool.map, verbose)
         _run([cc + ["-shared", "-o", tmp] + objs + ["-lpthread"]], map, verbose)
     os.replace(tmp, LIB)
